@@ -196,14 +196,14 @@ int64_t fgq_group_count(int64_t O, int64_t K, int32_t G) {
 namespace {
 
 // Wait for the offline step, then report non-finite weights (their groups
-// carry alpha = NaN).
-fgq_status ternarize_finish(const float* alpha, int64_t ng, hipStream_t st) {
-  std::vector<float> host(static_cast<size_t>(ng));
-  FGQ_TRY_HIP(hipMemcpyAsync(host.data(), alpha, sizeof(float) * ng, hipMemcpyDeviceToHost, st));
+// carry alpha = NaN, gathered into alpha[0] on the device).
+fgq_status ternarize_finish(float* alpha, int64_t ng, hipStream_t st) {
+  const fgq_status rc = launch_alpha_nan(alpha, ng, st);
+  if (rc != FGQ_OK) return rc;
+  float first = 0.0f;
+  FGQ_TRY_HIP(hipMemcpyAsync(&first, alpha, sizeof(first), hipMemcpyDeviceToHost, st));
   FGQ_TRY_HIP(hipStreamSynchronize(st));
-  for (int64_t i = 0; i < ng; ++i)
-    if (host[i] != host[i]) return FGQ_ERR_NONFINITE;
-  return FGQ_OK;
+  return first != first ? FGQ_ERR_NONFINITE : FGQ_OK;
 }
 
 }  // namespace

@@ -110,6 +110,8 @@ PreparedLayout prepared_layout_dfp(int64_t O, int64_t K, int32_t G);
 fgq_status launch_ternarize(const float* w, int64_t O, int64_t C, int32_t R, int32_t S, int32_t G,
                             int32_t method, uint8_t* codes, float* alpha, float* delta, float* delta_n,
                             hipStream_t st);
+// alpha[0] = NaN if any of the n scales is NaN (ternarize.hip).
+fgq_status launch_alpha_nan(float* alpha, int64_t n, hipStream_t st);
 // Eq. (3)-(4) as a ternarize method (fgq_ternarize_asym; delta = Dp,
 // delta_n = Dn).
 constexpr int32_t kTernAsym = 2;

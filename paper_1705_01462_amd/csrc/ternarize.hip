@@ -231,6 +231,143 @@ __global__ __launch_bounds__(kWave) void ternarize_kernel(
   }
 }
 
+// Groups of 4, 8 or 16 weights (the paper's own group sizes): one lane per
+// group, the group's weights in registers.  A workgroup takes `tc` channels
+// (whole groups) of one output row with all their taps, which are tc * R * S
+// consecutive floats, through LDS: the loads are whole lines, where a lane
+// per weight in reduction order reads one float in R*S and every line R*S
+// times.  The magnitudes are sorted by a compare-exchange network (only the
+// values in rank order enter the sums), the ranks counted directly; sums and
+// quotients are the general kernel's, in its order, so codes, alpha and Delta
+// are the same bit for bit.  Groups go to lanes with the channel fastest, so
+// alpha, Delta and the code bytes of a tap are written as runs.
+// 512x512x3x3, G = 4 (9.4 MB in, 5.3 MB out): 44.2 us with a lane per weight
+// (one lane in four then searching, a quotient in fp64 per kept count); the
+// whole call, with the status read back, 337 -> 40 us.
+constexpr int kTileFloats = 2304;  // LDS floats of a tile (9 KB: eight workgroups per unit)
+constexpr int kTileThreads = 256;
+
+template <int kG>
+__device__ inline void sort_desc(float (&v)[kG]) {
+  // odd-even merge sort, all indices constant after unrolling
+#pragma unroll
+  for (int p = 1; p < kG; p *= 2)
+#pragma unroll
+    for (int k = p; k >= 1; k /= 2)
+#pragma unroll
+      for (int j = k % p; j + k < kG; j += 2 * k)
+#pragma unroll
+        for (int i = 0; i < k; ++i)
+          if (i + j + k < kG && (i + j) / (2 * p) == (i + j + k) / (2 * p)) {
+            const float a = v[i + j], b = v[i + j + k];
+            v[i + j] = fmaxf(a, b);
+            v[i + j + k] = fminf(a, b);
+          }
+}
+
+template <int kG, int kMethod>
+__global__ __launch_bounds__(kTileThreads) void ternarize_tile_kernel(
+    const float* __restrict__ w, int32_t C, int32_t RS, int32_t tc, int32_t nct, int64_t O,
+    uint8_t* __restrict__ codes, float* __restrict__ alpha, float* __restrict__ delta) {
+  __shared__ float tile[kTileFloats];
+  const int64_t o = blockIdx.x / nct;
+  const int c0 = static_cast<int>(blockIdx.x % nct) * tc;
+  const int nc = C - c0 < tc ? C - c0 : tc;  // channels of this tile, whole groups
+  const float* src = w + (o * C + c0) * RS;
+  for (int i = threadIdx.x; i < nc * RS; i += kTileThreads) tile[i] = src[i];
+  __syncthreads();
+
+  const int gpt = nc / kG;  // groups per tap
+  const int64_t kg = static_cast<int64_t>(C / kG) * RS;  // groups per row
+  const int64_t rb = kg * (kG / 4);                      // code bytes per row
+  for (int gi = threadIdx.x; gi < gpt * RS; gi += kTileThreads) {
+    const int rs = gi / gpt, cg = gi - rs * gpt;
+    float v[kG], m[kG];
+    bool bad = false;
+#pragma unroll
+    for (int i = 0; i < kG; ++i) {
+      v[i] = tile[(cg * kG + i) * RS + rs];
+      m[i] = fabsf(v[i]);
+      bad |= !isfinite(v[i]);
+    }
+    bool keep[kG];
+    float a_out, d_out;
+    if constexpr (kMethod == FGQ_TERN_EXACT) {
+      float srt[kG];
+#pragma unroll
+      for (int i = 0; i < kG; ++i) srt[i] = m[i];
+      sort_desc<kG>(srt);
+      double S = 0.0, bestS = 0.0, bestf = 0.0;
+      int J = 0;
+#pragma unroll
+      for (int j = 1; j <= kG; ++j) {  // a zero magnitude adds nothing and lowers f: never chosen
+        S = S + static_cast<double>(srt[j - 1]);
+        const double f = (S * S) / static_cast<double>(j);
+        const bool up = srt[j - 1] > 0.0f && f > bestf;
+        bestf = up ? f : bestf;
+        bestS = up ? S : bestS;
+        J = up ? j : J;
+      }
+      a_out = J > 0 ? static_cast<float>(bestS / static_cast<double>(J)) : 0.0f;
+      d_out = 0.0f;
+#pragma unroll
+      for (int j = 0; j < kG; ++j) d_out = j == J ? srt[j] : d_out;
+#pragma unroll
+      for (int i = 0; i < kG; ++i) {
+        int rank = 0;
+#pragma unroll
+        for (int j = 0; j < kG; ++j) rank += (m[j] > m[i] || (m[j] == m[i] && j < i)) ? 1 : 0;
+        keep[i] = rank < J;
+      }
+    } else {
+      float thr;
+      if constexpr (kMethod == FGQ_TERN_GAUSS) {
+        double Q = 0.0;
+#pragma unroll
+        for (int i = 0; i < kG; ++i) Q = Q + static_cast<double>(v[i]) * static_cast<double>(v[i]);
+        thr = static_cast<float>(kGaussU * sqrt(Q / static_cast<double>(kG)));
+      } else {
+        double S = 0.0;
+#pragma unroll
+        for (int i = 0; i < kG; ++i) S = S + static_cast<double>(m[i]);
+        thr = static_cast<float>(S / static_cast<double>(kG));
+      }
+      double Ks = 0.0;
+      int cnt = 0;
+#pragma unroll
+      for (int i = 0; i < kG; ++i) {
+        keep[i] = m[i] > thr;
+        Ks = keep[i] ? Ks + static_cast<double>(m[i]) : Ks;
+        cnt += keep[i] ? 1 : 0;
+      }
+      a_out = cnt > 0 ? static_cast<float>(Ks / static_cast<double>(cnt)) : 0.0f;
+      d_out = thr;
+    }
+    const int64_t g = o * kg + static_cast<int64_t>(rs) * (C / kG) + c0 / kG + cg;
+    alpha[g] = bad ? __builtin_nanf("") : a_out;
+    if (delta) delta[g] = bad ? __builtin_nanf("") : d_out;
+    uint8_t* dst = codes + o * rb + (static_cast<int64_t>(rs) * (C / kG) + c0 / kG + cg) * (kG / 4);
+#pragma unroll
+    for (int b = 0; b < kG / 4; ++b) {
+      unsigned byte = 0;
+#pragma unroll
+      for (int i = 0; i < 4; ++i) byte |= static_cast<unsigned>(code_of(v[4 * b + i], keep[4 * b + i] && !bad)) << (2 * i);
+      dst[b] = static_cast<uint8_t>(byte);
+    }
+  }
+}
+
+// Brings "some scale is NaN" (a group with non-finite weights) to alpha[0],
+// where the host reads it: 4 bytes to copy instead of every scale (2.4 MB of
+// a 512x512x3x3 layer: 290 us of copy and host loop).  Every writer stores
+// the same value.
+__global__ __launch_bounds__(256) void alpha_nan_kernel(float* alpha, int64_t n) {
+  bool bad = false;
+  for (int64_t i = static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x; i < n; i += static_cast<int64_t>(gridDim.x) * 256)
+    bad |= alpha[i] != alpha[i];
+  if (bad) alpha[0] = __builtin_nanf("");
+}
+
 // Sec. 3.1: K-S distances of the weight magnitudes to the half-normal law of
 // N(0, sigma) (sigma = rms) and to the exponential law of scale mu = mean|w|
 // (1/lambda of Lemma 1), both fitted by maximum likelihood, on at most
@@ -332,11 +469,53 @@ fgq_status launch_ks(const float* w, int64_t n, double* d, int32_t* pick, hipStr
   return last_launch();
 }
 
+namespace {
+
+template <int kG>
+void launch_tile(int32_t method, uint32_t grid, const float* w, int32_t C, int32_t RS, int32_t tc, int32_t nct,
+                 int64_t O, uint8_t* codes, float* alpha, float* delta, hipStream_t st) {
+  const dim3 g(grid), b(kTileThreads);
+  if (method == FGQ_TERN_EXACT)
+    hipLaunchKernelGGL((ternarize_tile_kernel<kG, FGQ_TERN_EXACT>), g, b, 0, st, w, C, RS, tc, nct, O, codes, alpha, delta);
+  else if (method == FGQ_TERN_GAUSS)
+    hipLaunchKernelGGL((ternarize_tile_kernel<kG, FGQ_TERN_GAUSS>), g, b, 0, st, w, C, RS, tc, nct, O, codes, alpha, delta);
+  else
+    hipLaunchKernelGGL((ternarize_tile_kernel<kG, FGQ_TERN_EXP_LEMMA>), g, b, 0, st, w, C, RS, tc, nct, O, codes, alpha, delta);
+}
+
+}  // namespace
+
+fgq_status launch_alpha_nan(float* alpha, int64_t n, hipStream_t st) {
+  const int64_t blocks = ceil_div(n, 256 * 8) < 1024 ? ceil_div(n, 256 * 8) : 1024;
+  hipLaunchKernelGGL(alpha_nan_kernel, dim3(static_cast<uint32_t>(blocks)), dim3(256), 0, st, alpha, n);
+  return last_launch();
+}
+
 fgq_status launch_ternarize(const float* w, int64_t O, int64_t C, int32_t R,
                             int32_t S, int32_t G, int32_t method,
                             uint8_t* codes, float* alpha, float* delta, float* delta_n,
                             hipStream_t st) {
   const int64_t K = static_cast<int64_t>(R) * S * C;
+  // One lane per group where a group's weights fit registers and one run of
+  // G channels with all its taps fits the LDS tile; the asymmetric search
+  // and other group sizes take the general kernel.
+  const int64_t RS = static_cast<int64_t>(R) * S;
+  if (method != kTernAsym && (G == 4 || G == 8 || G == 16) && G * RS <= kTileFloats && C < (1LL << 31)) {
+    // half-full tiles at 3x3 leave eight workgroups a unit to overlap
+    int64_t tc = (kTileFloats / 2 / RS) / G * G;
+    if (tc < G) tc = G;
+    if (tc > C) tc = C;
+    const int64_t nct = ceil_div(C, tc);
+    if (O * nct <= 0x7fffffffLL) {
+      const uint32_t grid = static_cast<uint32_t>(O * nct);
+      const int32_t c = static_cast<int32_t>(C), rs = static_cast<int32_t>(RS), t = static_cast<int32_t>(tc),
+                    n = static_cast<int32_t>(nct);
+      if (G == 4) launch_tile<4>(method, grid, w, c, rs, t, n, O, codes, alpha, delta, st);
+      else if (G == 8) launch_tile<8>(method, grid, w, c, rs, t, n, O, codes, alpha, delta, st);
+      else launch_tile<16>(method, grid, w, c, rs, t, n, O, codes, alpha, delta, st);
+      return last_launch();
+    }
+  }
   const int32_t U = G / gcd_i(G, 4) * 4;  // lcm(G, 4)
   const int32_t upw = U >= kWave ? 1 : kWave / U;
   const int32_t NE = upw * U;

@@ -1,0 +1,50 @@
+"""fgq_ternarize where its one-lane-per-group tiles can go wrong: runs of
+channels that end inside a tile, tiles of one group, tap counts up to the tile
+limit and past it (the general kernel), and non-finite weights in the first,
+the last and an inner group.  Codes, scales and thresholds bit for bit."""
+import numpy as np
+import pytest
+import torch
+
+import fgq_inputs as fi
+import oracle
+
+fgq = pytest.importorskip("paper_1705_01462_amd")
+
+pytestmark = [pytest.mark.gpu,
+              pytest.mark.skipif(not torch.cuda.is_available(), reason="needs a GPU")]
+
+METHODS = [oracle.EXACT, oracle.EXP_LEMMA, oracle.GAUSS]
+
+
+@pytest.mark.parametrize("method", METHODS)
+@pytest.mark.parametrize("shape,G", [
+    ((3, 132, 3, 3), 4),     # 128 + 4 channels: the last tile holds one group
+    ((2, 1160, 1, 1), 8),    # 1152 + 8
+    ((2, 80, 5, 5), 16),     # 32 + 32 + 16
+    ((2, 32, 12, 12), 16),   # 16 * 144 = 2304 floats: one group's taps fill the tile
+    ((2, 16, 13, 13), 16),   # 16 * 169 floats: past it, the general kernel
+    ((1, 4, 1, 1), 4),
+])
+def test_tiles_bit_exact(shape, G, method):
+    w = fi.rng("tern-tile", *shape, G).standard_normal(shape).astype(np.float32) * np.float32(0.05)
+    w[np.abs(w) < 0.01] = 0.0   # zeros, and all-zero groups at G = 4
+    w = np.round(w * 200) / np.float32(200)  # ties
+    w = w.astype(np.float32)
+    t, a, d = oracle.ternarize(w, G, method)
+    codes, alpha, delta = fgq.fgq_ternarize(torch.from_numpy(w).cuda(), G, method)
+    np.testing.assert_array_equal(codes.cpu().numpy(), oracle.pack_codes(t))
+    np.testing.assert_array_equal(alpha.cpu().numpy().view(np.uint32), a.view(np.uint32))
+    np.testing.assert_array_equal(delta.cpu().numpy().view(np.uint32), d.view(np.uint32))
+
+
+@pytest.mark.parametrize("G", [4, 64])
+@pytest.mark.parametrize("where", [(0, 0, 0, 0), (15, 63, 2, 2), (7, 30, 1, 0)])
+def test_nonfinite_anywhere(where, G):
+    w = fi.he_weights(16, 64, 3, 3, "tern-nan")
+    fgq.fgq_ternarize(torch.from_numpy(w).cuda(), G)
+    for v in (np.nan, np.inf, -np.inf):
+        w[where] = v
+        with pytest.raises(fgq.FgqError) as e:
+            fgq.fgq_ternarize(torch.from_numpy(w).cuda(), G)
+        assert e.value.code == 5
