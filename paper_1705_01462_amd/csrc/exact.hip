@@ -53,21 +53,119 @@ __device__ inline int64_t a_index(const ConvGeom& g, int64_t m, int64_t k) {
   return ((b * g.H + hi) * g.W + wi) * g.C + c;
 }
 
+// A workgroup owns 64 rows x 64 channels and walks K in chunks of 64: the
+// chunk's activations, codes (expanded to int8) and the scales of the groups
+// that end in it are staged in LDS, the next chunk's loads are in flight
+// while the current one is computed, and a thread owns 4 x 4 outputs.
+//
+// Bound: the vector ALU (per group and output a conversion to fp64 and a
+// multiply-add, per four products one dot4).  The rows' (b, ho, wo) are
+// decoded once, the taps once per chunk, group ends are counted, and all
+// index arithmetic is in I (32 bits unless a size needs 64); with 64-bit
+// divisions for every loaded word and every four products, and the scales
+// fetched from memory at each group's end, they were what the kernel spent
+// its time on: 86.0 -> 35.1 us a call on a 3x3 layer of 40 -> 100 channels,
+// 8 x 29 x 31, G = 4.
+//
 // kVec: C % 4 == 0, so four consecutive k share one tap and are contiguous.
-template <int kBits, bool kVec, bool kDot4, int kOut>
+// kDot4: G % 4 == 0, so groups end on words of four k.
+template <int kBits, bool kVec, bool kDot4, int kOut, class I>
 __global__ __launch_bounds__(256) void exact_conv_kernel(
     const uint8_t* __restrict__ q, const float* __restrict__ sxp,
     const uint8_t* __restrict__ codes, const float* __restrict__ alpha,
     ConvGeom g, LayerOut out) {
+  constexpr int kMaxGr = kDot4 ? kKC / 4 : kKC;  // groups that end in a chunk, at most
+  constexpr int kAPitch = kMaxGr + 1;
   __shared__ __attribute__((aligned(16))) int8_t As[kTM * kStride];
   __shared__ __attribute__((aligned(16))) int8_t Ts[kTO * kStride];
+  __shared__ float Al[kTO * kAPitch];
   const int tid = threadIdx.x;
   const int tx = tid % 16, ty = tid / 16;
   const int64_t m0 = static_cast<int64_t>(blockIdx.x) * kTM;
   const int64_t o0 = static_cast<int64_t>(blockIdx.y) * kTO;
+  const I K = static_cast<I>(g.K), C = static_cast<I>(g.C), H = static_cast<I>(g.H), W = static_cast<I>(g.W);
+  const int32_t G = g.G;
   const int64_t ng = g.K / g.G;
   const int64_t rb = ceil_div(g.K, 4);
   const uint32_t xor_mask = kBits == 8 ? 0x80808080u : 0u;
+  const bool codes4 = rb % 4 == 0 && reinterpret_cast<uintptr_t>(codes) % 4 == 0;
+
+  // This thread's four activation rows (ty + 16*it) and its word of the chunk.
+  I hi0[4], wi0[4], rowb[4];
+  bool rowok[4];
+#pragma unroll
+  for (int it = 0; it < 4; ++it) {
+    const int64_t m = m0 + ty + 16 * it;
+    rowok[it] = m < g.M;
+    const I mm = rowok[it] ? static_cast<I>(m) : 0;
+    const I wo = mm % static_cast<I>(g.Wo);
+    const I t = mm / static_cast<I>(g.Wo);
+    const I ho = t % static_cast<I>(g.Ho);
+    hi0[it] = ho * g.sh - g.ph;
+    wi0[it] = wo * g.sw - g.pw;
+    rowb[it] = (t / static_cast<I>(g.Ho)) * H;
+  }
+  // Its code column and scale column (64 columns, four threads each).
+  const int col = tid / 4, part = tid % 4;
+  const bool colok = o0 + col < g.O;
+  const uint8_t* crow = codes + (o0 + (colok ? col : 0)) * rb;
+  const float* arow = alpha + (o0 + (colok ? col : 0)) * ng;
+
+  uint32_t aw[4], cw;
+  float al[kMaxGr / 4];
+  auto load = [&](I kc) {
+    const I k = kc + 4 * tx;
+#pragma unroll
+    for (int it = 0; it < 4; ++it) aw[it] = 0;
+    if constexpr (kVec) {
+      const I rs = k / C, c = k - rs * C;
+      const I r = rs / g.S, s = rs - r * g.S;
+#pragma unroll
+      for (int it = 0; it < 4; ++it) {
+        const I hi = hi0[it] + r, wi = wi0[it] + s;
+        if (rowok[it] && k < K && hi >= 0 && hi < H && wi >= 0 && wi < W) {
+          const I e = ((rowb[it] + hi) * W + wi) * C + c;
+          if (kBits == 8) {
+            aw[it] = *reinterpret_cast<const uint32_t*>(q + e);
+          } else {
+            const uint32_t h = *reinterpret_cast<const uint16_t*>(q + e / 2);
+            aw[it] = (h & 0xFu) | ((h & 0xF0u) << 4) | ((h & 0xF00u) << 8) | ((h & 0xF000u) << 12);
+          }
+        }
+      }
+    } else {
+#pragma unroll
+      for (int b = 0; b < 4; ++b) {
+        const I rs = (k + b) / C, c = (k + b) - rs * C;
+        const I r = rs / g.S, s = rs - r * g.S;
+#pragma unroll
+        for (int it = 0; it < 4; ++it) {
+          const I hi = hi0[it] + r, wi = wi0[it] + s;
+          if (rowok[it] && k + b < K && hi >= 0 && hi < H && wi >= 0 && wi < W)
+            aw[it] |= act_elem(q, kBits, ((rowb[it] + hi) * W + wi) * C + c) << (8 * b);
+        }
+      }
+    }
+    cw = 0;
+    const int64_t byte = kc / 4 + 4 * part;
+    if (colok) {
+      if (codes4) {
+        if (byte < rb) cw = *reinterpret_cast<const uint32_t*>(crow + byte);
+      } else {
+#pragma unroll
+        for (int b = 0; b < 4; ++b)
+          if (byte + b < rb) cw |= static_cast<uint32_t>(crow[byte + b]) << (8 * b);
+      }
+    }
+    // scales of the groups that end in the chunk
+    const int64_t g0 = kc / G;
+    const int ngc = static_cast<int>((kc + kKC < K ? kc + kKC : K) / G - g0);
+#pragma unroll
+    for (int i = 0; i < kMaxGr / 4; ++i) {
+      const int gi = part + 4 * i;
+      al[i] = colok && gi < ngc ? arow[g0 + gi] : 0.0f;
+    }
+  };
 
   double acc[4][4];
   int32_t P[4][4];
@@ -81,60 +179,41 @@ __global__ __launch_bounds__(256) void exact_conv_kernel(
       P[i][j] = 0;
     }
   }
+  int32_t left = G;  // weights left in the current group
 
-  for (int64_t kc = 0; kc < g.K; kc += kKC) {
-    // ---- activation tile A[64][64] (int8, offset for u8) ----
+  // The current group's scaled sums into the fp64 accumulators, `gi` its
+  // index among those that end in this chunk.
+  auto fold = [&](int gi) {
 #pragma unroll
-    for (int it = 0; it < 4; ++it) {
-      const int wid = tid + 256 * it;      // 1024 words of 4 k
-      const int r = wid / 16, wd = wid % 16;
-      const int64_t m = m0 + r;
-      const int64_t k = kc + 4 * wd;
-      uint32_t word = 0;
-      if (m < g.M) {
-        if (kVec) {
-          if (k < g.K) {
-            const int64_t e = a_index(g, m, k);
-            if (e >= 0) {
-              if (kBits == 8) {
-                word = *reinterpret_cast<const uint32_t*>(q + e);
-              } else {
-                const uint32_t h = *reinterpret_cast<const uint16_t*>(q + e / 2);
-                word = (h & 0xFu) | ((h & 0xF0u) << 4) | ((h & 0xF00u) << 8) | ((h & 0xF000u) << 12);
-              }
-            }
-          }
-        } else {
+    for (int j = 0; j < 4; ++j) {
+      const double a = static_cast<double>(Al[(tx + 16 * j) * kAPitch + gi]);
 #pragma unroll
-          for (int b = 0; b < 4; ++b) {
-            if (k + b < g.K) {
-              const int64_t e = a_index(g, m, k + b);
-              if (e >= 0) word |= act_elem(q, kBits, e) << (8 * b);
-            }
-          }
-        }
+      for (int i = 0; i < 4; ++i) {
+        const int32_t pt = P[i][j] + 128 * T[j];
+        acc[i][j] = fma(a, static_cast<double>(pt), acc[i][j]);
+        P[i][j] = 0;
       }
-      *reinterpret_cast<uint32_t*>(&As[r * kStride + 4 * wd]) = word ^ xor_mask;
+      T[j] = 0;
     }
-    // ---- code tile T[64][64] (int8 in {-1,0,1}) ----
-    {
-      const int col = tid / 4, part = tid % 4;  // 4 code bytes per thread
-      const int64_t o = o0 + col;
+  };
+
+  load(0);
+  for (I kc = 0; kc < K; kc += kKC) {
 #pragma unroll
-      for (int b = 0; b < 4; ++b) {
-        const int64_t byte = kc / 4 + part * 4 + b;
-        uint32_t cb = 0;
-        if (o < g.O && byte < rb) cb = codes[o * rb + byte];
-        *reinterpret_cast<uint32_t*>(&Ts[col * kStride + 4 * (part * 4 + b)]) = unpack_code_byte(cb);
-      }
-    }
+    for (int it = 0; it < 4; ++it)
+      *reinterpret_cast<uint32_t*>(&As[(ty + 16 * it) * kStride + 4 * tx]) = aw[it] ^ xor_mask;
+#pragma unroll
+    for (int b = 0; b < 4; ++b)
+      *reinterpret_cast<uint32_t*>(&Ts[col * kStride + 4 * (part * 4 + b)]) = unpack_code_byte((cw >> (8 * b)) & 0xFFu);
+#pragma unroll
+    for (int i = 0; i < kMaxGr / 4; ++i) Al[col * kAPitch + part + 4 * i] = al[i];
     __syncthreads();
+    if (kc + kKC < K) load(kc + kKC);
 
-    const int64_t kend = (g.K - kc) < kKC ? (g.K - kc) : kKC;
-    if (kDot4) {
-      // G % 4 == 0: groups end on word boundaries.
-      for (int wd = 0; wd < kKC / 4; ++wd) {
-        if (4 * wd >= kend) break;
+    const int kend = static_cast<int>(K - kc < kKC ? K - kc : kKC);
+    int gi = 0;
+    if constexpr (kDot4) {
+      for (int wd = 0; 4 * wd < kend; ++wd) {
         int32_t a[4], t[4];
 #pragma unroll
         for (int i = 0; i < 4; ++i) a[i] = *reinterpret_cast<const int32_t*>(&As[(ty + 16 * i) * kStride + 4 * wd]);
@@ -148,26 +227,14 @@ __global__ __launch_bounds__(256) void exact_conv_kernel(
 #pragma unroll
           for (int j = 0; j < 4; ++j) T[j] = __builtin_amdgcn_sdot4(t[j], 0x01010101, T[j], false);
         }
-        const int64_t kn = kc + 4 * wd + 4;
-        if (kn % g.G == 0) {
-          const int64_t gi = kn / g.G - 1;
-#pragma unroll
-          for (int j = 0; j < 4; ++j) {
-            const int64_t o = o0 + tx + 16 * j;
-            const double al = o < g.O ? static_cast<double>(alpha[o * ng + gi]) : 0.0;
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-              const int32_t pt = P[i][j] + 128 * T[j];
-              acc[i][j] = fma(al, static_cast<double>(pt), acc[i][j]);
-              P[i][j] = 0;
-            }
-            T[j] = 0;
-          }
+        left -= 4;
+        if (left == 0) {
+          fold(gi++);
+          left = G;
         }
       }
     } else {
-      for (int kk = 0; kk < kKC; ++kk) {
-        if (kk >= kend) break;
+      for (int kk = 0; kk < kend; ++kk) {
         int32_t a[4], t[4];
 #pragma unroll
         for (int i = 0; i < 4; ++i) a[i] = As[(ty + 16 * i) * kStride + kk];
@@ -181,21 +248,9 @@ __global__ __launch_bounds__(256) void exact_conv_kernel(
 #pragma unroll
           for (int j = 0; j < 4; ++j) T[j] += t[j];
         }
-        const int64_t kn = kc + kk + 1;
-        if (kn % g.G == 0) {
-          const int64_t gi = kn / g.G - 1;
-#pragma unroll
-          for (int j = 0; j < 4; ++j) {
-            const int64_t o = o0 + tx + 16 * j;
-            const double al = o < g.O ? static_cast<double>(alpha[o * ng + gi]) : 0.0;
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-              const int32_t pt = P[i][j] + 128 * T[j];
-              acc[i][j] = fma(al, static_cast<double>(pt), acc[i][j]);
-              P[i][j] = 0;
-            }
-            T[j] = 0;
-          }
+        if (--left == 0) {
+          fold(gi++);
+          left = G;
         }
       }
     }
@@ -252,14 +307,24 @@ fgq_status launch_exact_out(const uint8_t* q, const float* sx, const uint8_t* co
   const dim3 grid(static_cast<uint32_t>(gx), static_cast<uint32_t>(gy));
   const bool vec = (g.C % 4 == 0) && (reinterpret_cast<uintptr_t>(q) % 4 == 0);
   const bool dot4 = g.G % 4 == 0;
-  if (vec && dot4)
-    hipLaunchKernelGGL((exact_conv_kernel<kBits, true, true, kOut>), grid, dim3(256), 0, st, q, sx, codes, alpha, g, y);
-  else if (dot4)
-    hipLaunchKernelGGL((exact_conv_kernel<kBits, false, true, kOut>), grid, dim3(256), 0, st, q, sx, codes, alpha, g, y);
-  else if (vec)
-    hipLaunchKernelGGL((exact_conv_kernel<kBits, true, false, kOut>), grid, dim3(256), 0, st, q, sx, codes, alpha, g, y);
-  else
-    hipLaunchKernelGGL((exact_conv_kernel<kBits, false, false, kOut>), grid, dim3(256), 0, st, q, sx, codes, alpha, g, y);
+  // 32-bit indices while every row, element offset and reduction index
+  // (with a chunk's overhang) fits
+  const int64_t lim = (1LL << 31) - 4096;
+  const bool small = g.M < lim && g.K < lim && g.B * (g.H + 2 * g.ph) * (g.W + 2 * g.pw) < lim &&
+                     g.B * g.H * g.W * g.C < lim && g.H + 2LL * g.ph < lim && g.W + 2LL * g.pw < lim;
+  auto go = [&](auto v, auto d) {
+    constexpr bool kV = decltype(v)::value, kD = decltype(d)::value;
+    if (small)
+      hipLaunchKernelGGL((exact_conv_kernel<kBits, kV, kD, kOut, int32_t>), grid, dim3(256), 0, st, q, sx, codes, alpha, g, y);
+    else
+      hipLaunchKernelGGL((exact_conv_kernel<kBits, kV, kD, kOut, int64_t>), grid, dim3(256), 0, st, q, sx, codes, alpha, g, y);
+  };
+  using T = std::true_type;
+  using F = std::false_type;
+  if (vec && dot4) go(T{}, T{});
+  else if (dot4) go(F{}, T{});
+  else if (vec) go(T{}, F{});
+  else go(F{}, F{});
   return last_launch();
 }
 
