@@ -192,6 +192,12 @@ fgq_status launch_foldx_splitk(const uint8_t* q, const float* sx, const void* pr
 fgq_status launch_splitk_reduce(const int32_t* part, int32_t splits, bool dfp, int64_t M, int64_t O,
                                 const float* sx, const float* scale, const int32_t* fl, const LayerOut& out,
                                 hipStream_t st);
+// The same layers with K divided among a workgroup's waves (wavek.h), for
+// few tiles: whether a shape takes it, and the launch (kind: PrepKind of the
+// prepared buffer; callers check that kind's own *_supported first).
+bool wavek_pick(const ConvGeom& g, int kind);
+fgq_status launch_wavek(const uint8_t* q, const float* sx, const void* prepared, int kind, const ConvGeom& g,
+                        const LayerOut& out, hipStream_t st);
 // Per-group int8 MFMA kernel with an fp32 alpha epilogue (G = 64).
 bool group_supported(const ConvGeom& g, const uint8_t* q);
 fgq_status launch_group_conv(const uint8_t* q, const float* sx,
