@@ -106,14 +106,55 @@ __device__ inline void store_direct(const OutPtrs& out, const QScale& qs, int m_
   }
 }
 
+// A workgroup's residual values of a staged tile, in the order store_staged
+// uses them: requested before the tile's last matrix work, so that the store
+// phase does not wait for memory once per block (a first-stage ResNet-50
+// block at batch 64, whose last layer reads and writes 206 MB each: 211 ->
+// 150 us, the layer 151 -> 90).
+template <int kOut, int kNWO, int kNB>
+struct ResTile {
+  typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+  using T = EpiTile<kOut, kNWO>;
+  static constexpr int kPer = out_res(kOut) ? T::kChunks / 256 : 1;
+  static_assert(!out_res(kOut) || T::kChunks % 256 == 0, "whole chunks per thread");
+  u32x4 v[out_res(kOut) ? kNB : 1][kPer];
+
+  // block c of the tile at (m0, ot0)
+  __device__ void load(const float* res, int M, int O, int m0, int ot0, int tid, int c) {
+    if constexpr (out_res(kOut)) {
+#pragma unroll
+      for (int i = 0; i < kPer; ++i) {
+        const int t = 256 * i + tid;
+        const int lr = t / T::kChunksPerRow, cb = t % T::kChunksPerRow;
+        const int m = m0 + (lr / 32) * kNB * 32 + 32 * c + lr % 32;
+        const int ch = ot0 + cb * T::kChanPerChunk;
+        v[c][i] = u32x4{0, 0, 0, 0};
+        if (m < M && ch < O)
+          v[c][i] = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(res + static_cast<int64_t>(m) * O + ch));
+      }
+    }
+  }
+  __device__ void load(const float* res, int M, int O, int m0, int ot0, int tid) {
+    if constexpr (out_res(kOut)) {
+#pragma unroll
+      for (int c = 0; c < kNB; ++c) load(res, M, O, m0, ot0, tid, c);
+    }
+  }
+};
+struct NoNext {
+  __device__ void operator()(int) const {}
+};
+
 // Staged form (see above).  Every thread of the workgroup must call it;
 // `lds` holds at least EpiTile<kOut, kNWO>::kBytes and is free on entry
 // except for reads still in flight, which the first barrier waits for.
 // m0 / ot0: the workgroup's first row and channel; wm / wo: the wave's row
-// and channel position in the tile.
-template <int kOut, int kNWO, int kNB, bool kRcp, class Val>
+// and channel position in the tile; `next(c)` runs once block c's residual
+// has been used.
+template <int kOut, int kNWO, int kNB, bool kRcp, class Val, class Next = NoNext>
 __device__ inline void store_staged(unsigned char* lds, const OutPtrs& out, const QScale& qs, int m0, int ot0,
-                                    int wm, int wo, int tid, Val&& val) {
+                                    int wm, int wo, int tid, const ResTile<kOut, kNWO, kNB>& res, Val&& val,
+                                    Next&& next = Next()) {
   using T = EpiTile<kOut, kNWO>;
   typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
   constexpr bool kF32 = out_f32(kOut);
@@ -154,8 +195,7 @@ __device__ inline void store_staged(unsigned char* lds, const OutPtrs& out, cons
           const int64_t byte = 4 * el;
           if (check_store(kSiteStoreY, byte, 16, 4 * n)) {
             if constexpr (out_res(kOut)) {
-              const u32x4 rv = __builtin_nontemporal_load(
-                  reinterpret_cast<const u32x4*>(reinterpret_cast<const unsigned char*>(out.res) + byte));
+              const u32x4 rv = res.v[c][t0 / 256];
 #pragma unroll
               for (int i = 0; i < 4; ++i) w[i] = __float_as_uint(add_relu(__uint_as_float(w[i]), __uint_as_float(rv[i])));
             }
@@ -182,6 +222,7 @@ __device__ inline void store_staged(unsigned char* lds, const OutPtrs& out, cons
         }
       }
     }
+    next(c);
   }
 }
 

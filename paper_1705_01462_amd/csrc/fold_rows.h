@@ -14,7 +14,8 @@
 // tile's activation loads are issued before the current tile's matrix work
 // and output stores, so their latency is hidden behind them (the memory
 // counter is in order: loads issued before the stores are waited for
-// without waiting for the stores).
+// without waiting for the stores).  A residual is requested a tile ahead, as
+// the current tile's is used up.
 //
 // With one weight plane (fixed-point scales) a tile's weights are 16 KB and
 // the one-tile kernel, whose workgroups overlap on a compute unit, measured
@@ -37,8 +38,9 @@ __global__ __launch_bounds__(kThreads, 2) void fold_rows_kernel(FoldArgs a) {
   constexpr int kTO = 32 * kNWO;  // 128 channels
   constexpr int kTM = kNB * 32;   // 64 rows
   using Stager = StagerFor<kBits, kTM, kCM>;
-  constexpr int kLds = Stager::kStage > EpiTile<kOut, kNWO>::kBytes ? Stager::kStage : EpiTile<kOut, kNWO>::kBytes;
-  __shared__ __attribute__((aligned(16))) unsigned char lds[kLds];
+  // the epilogue's tile beside the activations: the second block's fragments
+  // are read after the first block's stores
+  __shared__ __attribute__((aligned(16))) unsigned char lds[Stager::kStage], tile[EpiTile<kOut, kNWO>::kBytes];
 
   const int tid = threadIdx.x;
   const int lane = tid % 64, wo = tid / 64;
@@ -77,23 +79,21 @@ __global__ __launch_bounds__(kThreads, 2) void fold_rows_kernel(FoldArgs a) {
   const OutPtrs out{a.y, a.qo, a.x.M, a.x.O, a.res};
   const bool staged = a.staged != 0;
 
+  const float os = out_scale_of<kOut>(a.oscale);
+  ResTile<kOut, kNWO, 1> res[kNB];
+
   int mt = blockIdx.x / a.x.n_otiles;
   Stager xs;
   if (mt < a.x.n_mtiles) {
     xs.init(a.x, mt * kTM, tid, 0);
     xs.load(a.x);
+    if (staged) {
+#pragma unroll
+      for (int c = 0; c < kNB; ++c) res[c].load(a.res, a.x.M, a.x.O, mt * kTM + 32 * c, ot * kTO, tid);
+    }
   }
   for (; mt < a.x.n_mtiles; mt += mstride) {
     const int m0 = mt * kTM;
-    v16i acc[kPlanes][kNB];
-#pragma unroll
-    for (int j = 0; j < kPlanes; ++j) {
-      v16i init;
-#pragma unroll
-      for (int r = 0; r < 16; ++r) init[r] = bias[j];
-#pragma unroll
-      for (int c = 0; c < kNB; ++c) acc[j][c] = init;
-    }
     __syncthreads();  // the previous tile's LDS reads (fragments, staged epilogue) are done
     xs.store(lds, 0x80808080u);  // q - 128 (padding 0 -> -128)
     __syncthreads();
@@ -101,31 +101,38 @@ __global__ __launch_bounds__(kThreads, 2) void fold_rows_kernel(FoldArgs a) {
       xs.init(a.x, m0 + mstride * kTM, tid, 0);
       xs.load(a.x);
     }
+    // One 32-row block at a time, matrix work and stores: its 48 accumulators
+    // leave registers for the residual tile and the resident weights.
 #pragma unroll
-    for (int h = 0; h < 4; ++h) {
-      v4i xf[kNB];
+    for (int c = 0; c < kNB; ++c) {
+      v16i acc[kPlanes];
 #pragma unroll
-      for (int c = 0; c < kNB; ++c) xf[c] = *reinterpret_cast<const v4i*>(lds + afrag[c][h]);
+      for (int j = 0; j < kPlanes; ++j)
 #pragma unroll
-      for (int c = 0; c < kNB; ++c)
+        for (int r = 0; r < 16; ++r) acc[j][r] = bias[j];
 #pragma unroll
-        for (int j = 0; j < kPlanes; ++j)
-          acc[j][c] = __builtin_amdgcn_mfma_i32_32x32x32_i8(xf[c], w[j][h], acc[j][c], 0, 0, 0);
+      for (int h = 0; h < 4; ++h) {
+        const v4i xf = *reinterpret_cast<const v4i*>(lds + afrag[c][h]);
+#pragma unroll
+        for (int j = 0; j < kPlanes; ++j) acc[j] = __builtin_amdgcn_mfma_i32_32x32x32_i8(xf, w[j][h], acc[j], 0, 0, 0);
+      }
+      auto val = [&](int, int r) {
+        const float f2 = static_cast<float>(acc[2][r]);
+        const float f1 = static_cast<float>(acc[1][r]);
+        const float f0 = static_cast<float>(acc[0][r]);
+        return fmaf(f2, c2, fmaf(f1, c1, f0 * c0));
+      };
+      with_out_scale<kOut>(os, [&](const QScale& qs, auto rcp) {
+        constexpr bool kR = decltype(rcp)::value;
+        if (staged)
+          store_staged<kOut, kNWO, 1, kR>(tile, out, qs, m0 + 32 * c, ot * kTO, 0, wo, tid, res[c], val, [&](int) {
+            if (mt + mstride < a.x.n_mtiles)
+              res[c].load(a.res, a.x.M, a.x.O, m0 + mstride * kTM + 32 * c, ot * kTO, tid);
+          });
+        else
+          store_direct<kOut, 1, kR>(out, qs, m0 + 32 * c, o, lane, val);
+      });
     }
-
-    auto val = [&](int c, int r) {
-      const float f2 = static_cast<float>(acc[2][c][r]);
-      const float f1 = static_cast<float>(acc[1][c][r]);
-      const float f0 = static_cast<float>(acc[0][c][r]);
-      return fmaf(f2, c2, fmaf(f1, c1, f0 * c0));
-    };
-    with_out_scale<kOut>(a.oscale, [&](const QScale& qs, auto rcp) {
-      constexpr bool kR = decltype(rcp)::value;
-      if (staged)
-        store_staged<kOut, kNWO, kNB, kR>(lds, out, qs, m0, ot * kTO, 0, wo, tid, val);
-      else
-        store_direct<kOut, kNB, kR>(out, qs, m0, o, lane, val);
-    });
   }
 }
 

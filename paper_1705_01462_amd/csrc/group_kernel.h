@@ -92,6 +92,11 @@ __global__ __launch_bounds__(kThreads, 2) void group_conv_kernel(GroupArgs a) {
   // addressing past the end of the buffer.
   const int abase = o0 + lane % 32 < a.O32 ? 4 * (o0 + lane % 32) : static_cast<int>(kOutOfRange);
 
+  // the epilogue's scalars, requested now
+  const float sx = *a.sx;
+  const float os = out_scale_of<kOut>(a.oscale);
+  ResTile<kOut, kNWO, kNB> res;
+
   Stager xs;
   xs.init(a.x, m0, tid);
 
@@ -177,24 +182,36 @@ __global__ __launch_bounds__(kThreads, 2) void group_conv_kernel(GroupArgs a) {
   xs.load(a.x);
   xs.store(lds, kMask);
   __syncthreads();
+  // The last step prefetches and publishes nothing; a residual is requested
+  // before its matrix work.
+  auto last = [&](auto U) {
+    constexpr int u = decltype(U)::value;
+    if (a.staged) res.load(a.res, a.x.M, a.x.O, m0, o0 - 32 * wo, tid);
+    __builtin_amdgcn_sched_barrier(0);
+    compute(u, cring[u], aring[u]);
+  };
   int ks = 0;
-  for (; ks + 2 <= nk; ks += 2) {
+  for (; ks + 3 <= nk; ks += 2) {
     step(I0{}, ks);
     step(I1{}, ks + 1);
   }
-  if (ks < nk) step(I0{}, ks);
+  if (ks + 2 <= nk) {
+    step(I0{}, ks);
+    last(I1{});
+  } else {
+    last(I0{});
+  }
 
   // ---- epilogue: lane holds rows m of channel o.
   const int o = o0 + lane % 32;
-  const float sx = *a.sx;
   // locals: a byte store may alias anything, including the argument block
   const OutPtrs out{a.y, a.qo, a.x.M, a.x.O, a.res};
   const bool staged = a.staged != 0;
-  with_out_scale<kOut>(a.oscale, [&](const QScale& qs, auto rcp) {
+  with_out_scale<kOut>(os, [&](const QScale& qs, auto rcp) {
     constexpr bool kR = decltype(rcp)::value;
     auto val = [&](int c, int r) { return acc[c][r] * sx; };
     if (staged)
-      store_staged<kOut, kNWO, kNB, kR>(lds, out, qs, m0, o0 - 32 * wo, wm, wo, tid, val);
+      store_staged<kOut, kNWO, kNB, kR>(lds, out, qs, m0, o0 - 32 * wo, wm, wo, tid, res, val);
     else
       store_direct<kOut, kNB, kR>(out, qs, m0 + wm * kNB * 32, o, lane, val);
   });

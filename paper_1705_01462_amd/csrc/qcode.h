@@ -113,17 +113,26 @@ __device__ inline void emit_out(float* y, uint8_t* q, const QScale& qs, int64_t 
 }
 
 // The store loop of a layer epilogue, run as f(qs, rcp) with the output
-// kind's scale: for codes, qs is the scale read from `scale` and rcp the
-// reciprocal-form flag as a type (see with_rcp); for fp32 output neither is
-// used.
+// kind's scale: for codes, qs is the scale and rcp the reciprocal-form flag
+// as a type (see with_rcp); for fp32 output neither is used.
 template <int kOut, class F>
-__device__ inline void with_out_scale(const float* scale, F&& f) {
+__device__ inline void with_out_scale(float scale, F&& f) {
   if constexpr (out_code_bits(kOut) == 0) {
     f(QScale{}, std::true_type{});
   } else {
-    const QScale qs = make_qscale(*scale, out_code_bits(kOut));
+    const QScale qs = make_qscale(scale, out_code_bits(kOut));
     with_rcp(qs, [&](auto rcp) { f(qs, rcp); });
   }
+}
+// The same with the scale read from device memory (only for codes).  Kernels
+// that can, read it at their start (out_scale_of) and pass the value.
+template <int kOut>
+__device__ inline float out_scale_of(const float* scale) {
+  return out_code_bits(kOut) == 0 ? 1.0f : *scale;
+}
+template <int kOut, class F>
+__device__ inline void with_out_scale(const float* scale, F&& f) {
+  with_out_scale<kOut>(out_scale_of<kOut>(scale), f);
 }
 
 }  // namespace fgq

@@ -8,7 +8,7 @@
 // compute units that chain is the layer's time: 17.6 us (fixed-point scales)
 // to 28.6 us (groups of 64) for the 3x3 layer of 512 channels at 7 x 7,
 // batch 1 (4 tiles of 36 steps), 6.9 and 6.8 us here, and ResNet-50's whole
-// forward pass at batch 1 594 -> 344 us.  Here
+// forward pass at batch 1 594 -> 321 us.  Here
 //  * a wave takes every kWK-th step of the reduction and loads both operands
 //    straight into matrix-instruction fragments, two steps ahead, with no LDS
 //    and no barrier on the way: lane l holds row l % 32, k-slot 16 * (l / 32)
