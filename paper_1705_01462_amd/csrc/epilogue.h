@@ -111,22 +111,23 @@ __device__ inline void store_direct(const OutPtrs& out, const QScale& qs, int m_
 // phase does not wait for memory once per block (a first-stage ResNet-50
 // block at batch 64, whose last layer reads and writes 206 MB each: 211 ->
 // 150 us, the layer 151 -> 90).
-template <int kOut, int kNWO, int kNB>
+// kBlocks of the wave's kNB blocks (row stride), from block c0 on.
+template <int kOut, int kNWO, int kNB, int kBlocks = kNB>
 struct ResTile {
   typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
   using T = EpiTile<kOut, kNWO>;
   static constexpr int kPer = out_res(kOut) ? T::kChunks / 256 : 1;
   static_assert(!out_res(kOut) || T::kChunks % 256 == 0, "whole chunks per thread");
-  u32x4 v[out_res(kOut) ? kNB : 1][kPer];
+  u32x4 v[out_res(kOut) ? kBlocks : 1][kPer];
 
-  // block c of the tile at (m0, ot0)
-  __device__ void load(const float* res, int M, int O, int m0, int ot0, int tid, int c) {
+  // block c0 + c of the tile at (m0, ot0)
+  __device__ void load(const float* res, int M, int O, int m0, int ot0, int tid, int c, int c0) {
     if constexpr (out_res(kOut)) {
 #pragma unroll
       for (int i = 0; i < kPer; ++i) {
         const int t = 256 * i + tid;
         const int lr = t / T::kChunksPerRow, cb = t % T::kChunksPerRow;
-        const int m = m0 + (lr / 32) * kNB * 32 + 32 * c + lr % 32;
+        const int m = m0 + (lr / 32) * kNB * 32 + 32 * (c0 + c) + lr % 32;
         const int ch = ot0 + cb * T::kChanPerChunk;
         v[c][i] = u32x4{0, 0, 0, 0};
         if (m < M && ch < O)
@@ -134,10 +135,10 @@ struct ResTile {
       }
     }
   }
-  __device__ void load(const float* res, int M, int O, int m0, int ot0, int tid) {
+  __device__ void load(const float* res, int M, int O, int m0, int ot0, int tid, int c0 = 0) {
     if constexpr (out_res(kOut)) {
 #pragma unroll
-      for (int c = 0; c < kNB; ++c) load(res, M, O, m0, ot0, tid, c);
+      for (int c = 0; c < kBlocks; ++c) load(res, M, O, m0, ot0, tid, c, c0);
     }
   }
 };
@@ -149,12 +150,13 @@ struct NoNext {
 // `lds` holds at least EpiTile<kOut, kNWO>::kBytes and is free on entry
 // except for reads still in flight, which the first barrier waits for.
 // m0 / ot0: the workgroup's first row and channel; wm / wo: the wave's row
-// and channel position in the tile; `next(c)` runs once block c's residual
-// has been used.
-template <int kOut, int kNWO, int kNB, bool kRcp, class Val, class Next = NoNext>
+// and channel position in the tile; kBlocks of the waves' kNB blocks are
+// stored, from block cb0 on (val counts from 0); `next(c)` runs once block
+// c's residual has been used.
+template <int kOut, int kNWO, int kNB, bool kRcp, int kBlocks = kNB, class Val, class Next = NoNext>
 __device__ inline void store_staged(unsigned char* lds, const OutPtrs& out, const QScale& qs, int m0, int ot0,
-                                    int wm, int wo, int tid, const ResTile<kOut, kNWO, kNB>& res, Val&& val,
-                                    Next&& next = Next()) {
+                                    int wm, int wo, int tid, const ResTile<kOut, kNWO, kNB, kBlocks>& res, Val&& val,
+                                    Next&& next = Next(), int cb0 = 0) {
   using T = EpiTile<kOut, kNWO>;
   typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
   constexpr bool kF32 = out_f32(kOut);
@@ -162,7 +164,7 @@ __device__ inline void store_staged(unsigned char* lds, const OutPtrs& out, cons
   const int lane = tid % 64;
   const int col = 32 * wo + lane % 32;  // the lane's channel within the tile
 #pragma unroll
-  for (int c = 0; c < kNB; ++c) {
+  for (int c = 0; c < kBlocks; ++c) {
     __syncthreads();
 #pragma unroll
     for (int r = 0; r < 16; ++r) {
@@ -183,7 +185,7 @@ __device__ inline void store_staged(unsigned char* lds, const OutPtrs& out, cons
       const int t = t0 + tid;
       if (T::kChunks % 256 != 0 && t >= T::kChunks) break;
       const int lr = t / T::kChunksPerRow, cb = t % T::kChunksPerRow;
-      const int m = m0 + (lr / 32) * kNB * 32 + 32 * c + lr % 32;
+      const int m = m0 + (lr / 32) * kNB * 32 + 32 * (cb0 + c) + lr % 32;
       const int ch = ot0 + cb * T::kChanPerChunk;
       if (m < out.M && ch < out.O) {
         u32x4 w = *reinterpret_cast<const u32x4*>(lds + lr * T::kPitch + 16 * cb);

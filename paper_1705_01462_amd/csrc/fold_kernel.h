@@ -119,8 +119,8 @@ namespace {
 
 using namespace ig;
 
-template <int kBits, int kNWO, int kNB, int kCM, int kOut, bool kDfp, int kG>
-__global__ __launch_bounds__(kThreads, kNB <= 2 ? 2 : 1) void fold_conv_kernel(FoldArgs a) {
+template <int kBits, int kNWO, int kNB, int kCM, int kOut, bool kDfp, int kG, int kNWK = 1>
+__global__ __launch_bounds__(kThreads * kNWK, kNB <= 2 ? 2 : 1) void fold_conv_kernel(FoldArgs a) {
   constexpr int kNWM = 4 / kNWO;
   constexpr int kTO = 32 * kNWO;
   constexpr int kTM = kNWM * kNB * 32;
@@ -128,9 +128,15 @@ __global__ __launch_bounds__(kThreads, kNB <= 2 ? 2 : 1) void fold_conv_kernel(F
   constexpr int kXP = Stager::kXP;
   constexpr int kStage = Stager::kStage;
   constexpr int kLds = 2 * kStage > EpiTile<kOut, kNWO>::kBytes ? 2 * kStage : EpiTile<kOut, kNWO>::kBytes;
-  __shared__ __attribute__((aligned(16))) unsigned char lds[kLds];
+  constexpr int kXch = kNWK > 1 ? 4 * 16 * 64 * 4 : 0;  // bytes of one wave set's exchanged block
+  static_assert(kNWK == 1 || (kNWK == 2 && kNB == 2 && kDfp && kOut != 1 && kXch <= kLds), "two sets of four waves");
+  __shared__ __attribute__((aligned(16))) unsigned char lds_all[kNWK * kLds];
 
-  const int tid = threadIdx.x;
+  // kNWK = 2: two sets of four waves share the tile's K steps, each with its
+  // own activation stages.
+  const int tid = threadIdx.x % kThreads;
+  const int wk = kNWK > 1 ? __builtin_amdgcn_readfirstlane(threadIdx.x / kThreads) : 0;
+  unsigned char* const lds = lds_all + wk * kLds;
   const int lane = tid % 64, wave = tid / 64;
   const int wo = wave % kNWO, wm = wave / kNWO;
   // Workgroups of one K split are numbered together (they share activations).
@@ -146,7 +152,7 @@ __global__ __launch_bounds__(kThreads, kNB <= 2 ? 2 : 1) void fold_conv_kernel(F
   const float os = out_scale_of<kOut>(a.oscale);
   const int32_t fl = kDfp && kOut != 1 ? *a.fl : 0;
   const float sc = !kDfp && kOut != 1 && o0 + lane % 32 < a.x.O ? a.scale[o0 + lane % 32] : 0.0f;
-  ResTile<kOut, kNWO, kNB> res;
+  ResTile<kOut, kNWO, kNB, kNB / kNWK> res;
 
   // ---- weight fragments: lane supplies channel o0 + lane%32, k-slot
   // 16*(lane/32) of K half h; the fragment-ordered planes put the wave's
@@ -156,11 +162,14 @@ __global__ __launch_bounds__(kThreads, kNB <= 2 ? 2 : 1) void fold_conv_kernel(F
   const int wbase = (o0 / 32) * a.nks * kTileB + 16 * lane;
 
   const int nk_all = (a.x.K + kKT - 1) / kKT;
-  const int ks0 = split * a.steps_per_split;  // this workgroup's K steps [ks0, nk)
-  const int nk = ks0 + a.steps_per_split < nk_all ? ks0 + a.steps_per_split : nk_all;
+  // this workgroup's (wave set's) K steps [ks0, nk)
+  const int per_set = kNWK > 1 ? (nk_all + kNWK - 1) / kNWK : a.steps_per_split;
+  const int ks0 = (kNWK > 1 ? wk : split) * per_set;
+  const int nk = ks0 + per_set < nk_all ? ks0 + per_set : nk_all;
   Stager xs;
   xs.init(a.x, m0, tid, ks0);
-
+  constexpr bool kTwo = kNWK == 2;  // loads two steps ahead
+  
   // A step covers two 64-wide fragment blocks (K quarters hq = 2*blk + h).
   // The step is the scalar offset, which the buffer range check does not
   // cover, so a step past the last is clamped to the last one (those loads
@@ -360,10 +369,55 @@ __global__ __launch_bounds__(kThreads, kNB <= 2 ? 2 : 1) void fold_conv_kernel(F
   using I1 = std::integral_constant<int, 1>;
   load_w(I0{}, ks0);
   xs.load(a.x);
-  xs.store(lds, 0x80808080u);
-  __syncthreads();
   int ks = ks0;
-  if constexpr (kPlanes == 1 && kCM <= 1) {
+  if constexpr (!kTwo) {
+    xs.store(lds, 0x80808080u);
+    __syncthreads();
+  }
+  if constexpr (kTwo) {
+    // With one workgroup on a compute unit nothing else covers the loads'
+    // latency, so they run two steps ahead.  Step ks publishes the activations of step ks+1 (requested a
+    // step ago), requests those of ks+2, does its matrix work, and requests
+    // the weights of ks+2 into the registers it has just used; the memory
+    // counter is in order, so the publish leaves the younger weight loads in
+    // flight.  A set with a step fewer repeats its last weights on nothing.
+    Stager xs2 = xs;  // the odd steps' registers
+    xs2.advance(a.x);
+    xs2.load(a.x);
+    load_w(I1{}, ks0 + 1);
+    xs.store(lds, 0x80808080u);
+    __syncthreads();
+    auto step2 = [&](auto U, int k, Stager& pub, Stager& req) {
+      constexpr int u = decltype(U)::value;
+      pub.store(lds + (1 - u) * kStage, 0x80808080u);  // step k+1
+      req.advance2(a.x);
+      req.load(a.x);                                   // step k+2
+      __builtin_amdgcn_sched_barrier(0);
+      if (k < nk) compute(u, wring[u]);
+      __builtin_amdgcn_sched_barrier(0);
+      load_w(U, k + 2);
+      __syncthreads();
+    };
+    const int last = ks0 + per_set - 1;  // of either set
+    for (; ks + 2 <= last; ks += 2) {
+      step2(I0{}, ks, xs2, xs);
+      step2(I1{}, ks + 1, xs, xs2);
+    }
+    // The last step publishes nothing; a residual is requested before its
+    // matrix work.
+    auto finish = [&](auto U, int k) {
+      constexpr int u = decltype(U)::value;
+      if (a.staged) res.load(a.res, a.x.M, a.x.O, m0, o0 - 32 * wo, tid, wk);
+      __builtin_amdgcn_sched_barrier(0);
+      if (k < nk) compute(u, wring[u]);
+    };
+    if (ks < last) {
+      step2(I0{}, ks, xs2, xs);
+      finish(I1{}, ks + 1);
+    } else {
+      finish(I0{}, ks);
+    }
+  } else if constexpr (kPlanes == 1 && out_res(kOut)) {
     // The last step prefetches and publishes nothing; a residual is requested
     // before its matrix work.
     auto last = [&](auto U) {
@@ -383,9 +437,9 @@ __global__ __launch_bounds__(kThreads, kNB <= 2 ? 2 : 1) void fold_conv_kernel(F
       last(I0{});
     }
   } else {
-    // three planes: a second way into the epilogue would spill the 96
-    // accumulators; tiny C (two steps in all): 57.9 against 56.9 us on a
-    // 7x7 first layer of 64 images
+    // One way into the epilogue: a second one costs registers, which spill
+    // with three planes' 96 accumulators and cost one plane a workgroup per
+    // compute unit (14.7 -> 15.2 us, 128 -> 128 channels, 3x3, 28 x 28, batch 64).
     for (; ks + 2 <= nk; ks += 2) {
       step(I0{}, ks);
       step(I1{}, ks + 1);
@@ -416,36 +470,54 @@ __global__ __launch_bounds__(kThreads, kNB <= 2 ? 2 : 1) void fold_conv_kernel(F
     // locals: a byte store may alias anything, including the argument block
     const OutPtrs out{a.y, a.qo, a.x.M, a.x.O, a.res};
     const bool staged = a.staged != 0;
-    v16f yv[kNB];  // the tile's fp32 outputs
+    if constexpr (kNWK == 2) {
+      // The sets exchange a block each through LDS and add (integers, exact):
+      // set 0 finishes the waves' first blocks, set 1 the second.
+      __syncthreads();  // fragments read
+      int* const give = reinterpret_cast<int*>(lds_all + (1 - wk) * kLds) + wave * 16 * 64 + lane;
+      const int* const take = reinterpret_cast<const int*>(lds) + wave * 16 * 64 + lane;
+#pragma unroll
+      for (int r = 0; r < 16; ++r) give[64 * r] = wk == 0 ? acc[0][1][r] : acc[0][0][r];
+      __syncthreads();
+#pragma unroll
+      for (int r = 0; r < 16; ++r) acc[0][0][r] = (wk == 0 ? acc[0][0][r] : acc[0][1][r]) + take[64 * r];
+    }
+    constexpr int kBlocks = kNB / kNWK;
+    const int cb0 = kNWK > 1 ? wk : 0;
+    auto emit = [&](auto val) {
+      with_out_scale<kOut>(os, [&](const QScale& qs, auto rcp) {
+        constexpr bool kR = decltype(rcp)::value;
+        if (staged)
+          store_staged<kOut, kNWO, kNB, kR, kBlocks>(lds, out, qs, m0, o0 - 32 * wo, wm, wo, tid, res, val, NoNext(), cb0);
+        else
+          store_direct<kOut, kBlocks, kR>(out, qs, m0 + wm * kNB * 32 + 32 * cb0, o, lane, val);
+      });
+    };
     if constexpr (kDfp) {
       // y = fp32(double(S) * (double(s_x) * 2^-fl)); the scale is exact.
       // fl INT32_MIN marks rejected scales (never negated)
       const double cd = fl > -2048 && fl < 2048 ? static_cast<double>(sx) * ldexp(1.0, -fl) : 0.0;
-#pragma unroll
-      for (int c = 0; c < kNB; ++c)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) yv[c][r] = static_cast<float>(static_cast<double>(acc[0][c][r]) * cd);
+      emit([&](int c, int r) { return static_cast<float>(static_cast<double>(acc[0][c][r]) * cd); });
     } else {
       const float c0 = sx * sc;
       const float c1 = c0 * 255.0f, c2 = c0 * 65025.0f;
+      auto combine = [&](int c, int r) {
+        const float f2 = static_cast<float>(acc[2 % kPlanes][c][r]);
+        const float f1 = static_cast<float>(acc[1 % kPlanes][c][r]);
+        const float f0 = static_cast<float>(acc[0][c][r]);
+        return fmaf(f2, c2, fmaf(f1, c1, f0 * c0));
+      };
+      if constexpr (out_f32(kOut)) {
+        v16f yv[kNB];  // before the stores: frees the accumulators for the residual
 #pragma unroll
-      for (int c = 0; c < kNB; ++c)
+        for (int c = 0; c < kNB; ++c)
 #pragma unroll
-        for (int r = 0; r < 16; ++r) {
-          const float f2 = static_cast<float>(acc[2 % kPlanes][c][r]);
-          const float f1 = static_cast<float>(acc[1 % kPlanes][c][r]);
-          const float f0 = static_cast<float>(acc[0][c][r]);
-          yv[c][r] = fmaf(f2, c2, fmaf(f1, c1, f0 * c0));
-        }
+          for (int r = 0; r < 16; ++r) yv[c][r] = combine(c, r);
+        emit([&](int c, int r) { return yv[c][r]; });
+      } else {
+        emit(combine);
+      }
     }
-    auto val = [&](int c, int r) { return yv[c][r]; };
-    with_out_scale<kOut>(os, [&](const QScale& qs, auto rcp) {
-      constexpr bool kR = decltype(rcp)::value;
-      if (staged)
-        store_staged<kOut, kNWO, kNB, kR>(lds, out, qs, m0, o0 - 32 * wo, wm, wo, tid, res, val);
-      else
-        store_direct<kOut, kNB, kR>(out, qs, m0 + wm * kNB * 32, o, lane, val);
-    });
   }
 }
 
@@ -458,6 +530,20 @@ fgq_status launch_cfg(const FoldArgs& a0, hipStream_t st) {
   const int64_t n = static_cast<int64_t>(a.x.n_otiles) * a.x.n_mtiles * a.splits;
   if (n > 0x7fffffffLL) return FGQ_ERR_SHAPE;
   const dim3 grid(static_cast<uint32_t>(n));
+  if constexpr (kDfp && kOut != 1 && kNWO >= 2) {
+    // At most one workgroup per compute unit: a second set of waves halves
+    // its chain of K steps, an exposed load and a barrier each (us, one set
+    // -> two: 196 tiles of 36 steps 18.5 -> 15.4, of 16 10.6 -> 9.2, of 8
+    // 7.5 -> 6.8, of 4 5.9 -> 5.7; at fewer steps the exchange costs as much).
+    // With more tiles the other workgroup of the unit is that second set.
+    if (a.x.C % 16 == 0 && n <= device_cus() && a.x.K > 3 * kKT) {
+      if (a.x.C >= kKT)
+        hipLaunchKernelGGL((fold_conv_kernel<kBits, kNWO, kNB, 0, kOut, kDfp, kG, 2>), grid, dim3(2 * kThreads), 0, st, a);
+      else
+        hipLaunchKernelGGL((fold_conv_kernel<kBits, kNWO, kNB, 1, kOut, kDfp, kG, 2>), grid, dim3(2 * kThreads), 0, st, a);
+      return last_launch();
+    }
+  }
   switch (c_mode(a.x.C)) {
     case 0: hipLaunchKernelGGL((fold_conv_kernel<kBits, kNWO, kNB, 0, kOut, kDfp, kG>), grid, dim3(kThreads), 0, st, a); break;
     case 1: hipLaunchKernelGGL((fold_conv_kernel<kBits, kNWO, kNB, 1, kOut, kDfp, kG>), grid, dim3(kThreads), 0, st, a); break;

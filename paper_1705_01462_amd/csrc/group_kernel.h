@@ -182,24 +182,32 @@ __global__ __launch_bounds__(kThreads, 2) void group_conv_kernel(GroupArgs a) {
   xs.load(a.x);
   xs.store(lds, kMask);
   __syncthreads();
-  // The last step prefetches and publishes nothing; a residual is requested
-  // before its matrix work.
-  auto last = [&](auto U) {
-    constexpr int u = decltype(U)::value;
-    if (a.staged) res.load(a.res, a.x.M, a.x.O, m0, o0 - 32 * wo, tid);
-    __builtin_amdgcn_sched_barrier(0);
-    compute(u, cring[u], aring[u]);
-  };
   int ks = 0;
-  for (; ks + 3 <= nk; ks += 2) {
-    step(I0{}, ks);
-    step(I1{}, ks + 1);
-  }
-  if (ks + 2 <= nk) {
-    step(I0{}, ks);
-    last(I1{});
+  if constexpr (out_res(kOut)) {
+    // The last step prefetches and publishes nothing; the residual is
+    // requested before its matrix work.
+    auto last = [&](auto U) {
+      constexpr int u = decltype(U)::value;
+      if (a.staged) res.load(a.res, a.x.M, a.x.O, m0, o0 - 32 * wo, tid);
+      __builtin_amdgcn_sched_barrier(0);
+      compute(u, cring[u], aring[u]);
+    };
+    for (; ks + 3 <= nk; ks += 2) {
+      step(I0{}, ks);
+      step(I1{}, ks + 1);
+    }
+    if (ks + 2 <= nk) {
+      step(I0{}, ks);
+      last(I1{});
+    } else {
+      last(I0{});
+    }
   } else {
-    last(I0{});
+    for (; ks + 2 <= nk; ks += 2) {
+      step(I0{}, ks);
+      step(I1{}, ks + 1);
+    }
+    if (ks < nk) step(I0{}, ks);
   }
 
   // ---- epilogue: lane holds rows m of channel o.

@@ -135,6 +135,20 @@ struct ActStager {
     }
   }
 
+  // Two steps on.
+  __device__ void advance2(const ActArgs& a) {
+    if constexpr (kSmallC) {
+      tk += 2 * kKT;
+      const int t = ts + (tc + 2 * kKT) / a.C;
+      tc = (tc + 2 * kKT) % a.C;
+      tr += t / a.S;
+      ts = t % a.S;
+    } else {
+      advance(a);
+      advance(a);
+    }
+  }
+
   __device__ void load(const ActArgs& a) {
 #pragma unroll
     for (int i = 0; i < kXP; ++i) {
