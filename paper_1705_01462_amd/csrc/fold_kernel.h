@@ -473,9 +473,9 @@ __global__ __launch_bounds__(kThreads * kNWK, kNB <= 2 ? 2 : 1) void fold_conv_k
     if constexpr (kNWK == 2) {
       // The sets exchange a block each through LDS and add (integers, exact):
       // set 0 finishes the waves' first blocks, set 1 the second.
-      __syncthreads();  // fragments read
       int* const give = reinterpret_cast<int*>(lds_all + (1 - wk) * kLds) + wave * 16 * 64 + lane;
       const int* const take = reinterpret_cast<const int*>(lds) + wave * 16 * 64 + lane;
+      __syncthreads();  // fragments read
 #pragma unroll
       for (int r = 0; r < 16; ++r) give[64 * r] = wk == 0 ? acc[0][1][r] : acc[0][0][r];
       __syncthreads();
@@ -508,9 +508,9 @@ __global__ __launch_bounds__(kThreads * kNWK, kNB <= 2 ? 2 : 1) void fold_conv_k
         return fmaf(f2, c2, fmaf(f1, c1, f0 * c0));
       };
       if constexpr (out_f32(kOut)) {
-        v16f yv[kNB];  // before the stores: frees the accumulators for the residual
+        v16f yv[kBlocks];  // before the stores: frees the accumulators for the residual
 #pragma unroll
-        for (int c = 0; c < kNB; ++c)
+        for (int c = 0; c < kBlocks; ++c)
 #pragma unroll
           for (int r = 0; r < 16; ++r) yv[c][r] = combine(c, r);
         emit([&](int c, int r) { return yv[c][r]; });
@@ -530,12 +530,14 @@ fgq_status launch_cfg(const FoldArgs& a0, hipStream_t st) {
   const int64_t n = static_cast<int64_t>(a.x.n_otiles) * a.x.n_mtiles * a.splits;
   if (n > 0x7fffffffLL) return FGQ_ERR_SHAPE;
   const dim3 grid(static_cast<uint32_t>(n));
+  // At most one workgroup per compute unit: a second set of waves halves its
+  // chain of K steps, an exposed load and a barrier each (us, one set -> two:
+  // 196 tiles of 36 steps 18.5 -> 15.4, of 16 10.6 -> 9.2, of 8 7.5 -> 6.8, of
+  // 4 5.9 -> 5.7; at fewer steps the exchange costs as much).  With more tiles
+  // the other workgroup of the unit is that second set.  Three planes gain
+  // nothing (196 tiles of 36 steps 30.2 -> 30.6, of 8 10.2 -> 12.0): their
+  // steps are bound by matrix work and code expansion, not by the loads.
   if constexpr (kDfp && kOut != 1 && kNWO >= 2) {
-    // At most one workgroup per compute unit: a second set of waves halves
-    // its chain of K steps, an exposed load and a barrier each (us, one set
-    // -> two: 196 tiles of 36 steps 18.5 -> 15.4, of 16 10.6 -> 9.2, of 8
-    // 7.5 -> 6.8, of 4 5.9 -> 5.7; at fewer steps the exchange costs as much).
-    // With more tiles the other workgroup of the unit is that second set.
     if (a.x.C % 16 == 0 && n <= device_cus() && a.x.K > 3 * kKT) {
       if (a.x.C >= kKT)
         hipLaunchKernelGGL((fold_conv_kernel<kBits, kNWO, kNB, 0, kOut, kDfp, kG, 2>), grid, dim3(2 * kThreads), 0, st, a);

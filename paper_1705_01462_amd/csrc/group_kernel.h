@@ -15,8 +15,20 @@
 // (q XOR 0x7F, padding reads 0 -> 127), and each group's block accumulation
 // starts from -127 * sum_{k in g} t[o][k], which the matrix cores compute
 // from a constant operand once per group and channel block, so the block
-// result is exactly -P and the epilogue multiplies by -alpha.  uint4
-// activations (0..15) need no offset.
+// result is exactly -P and the epilogue multiplies by -alpha.
+//
+// uint4 activations take the 8-bit floating-point form of the instruction,
+// whose result is fp32: a byte 0..15 read as e4m3 is exactly that many 2^-9
+// (subnormals and the first binade are linear in the bits), the weights are
+// -1, 0, 1 in e4m3 and a block scale of 2^9 makes the sum the integer P again
+// (at most 64 * 15, exact).  One 64-deep instruction per group takes the time
+// of two 32-deep int8 ones, and P needs no conversion: the vector ALU, which
+// binds this kernel, does 16 multiply-adds per group and block instead of 32
+// operations (us, 256 channels, 3x3, 14 x 14, batch 64: 22.3 -> 19.0; 512
+// channels, 7 x 7, with two wave sets: 31.9 -> 20.3).  An fp32 output of one
+// K step keeps the int8 form: it is bound by its stores, which leave at a
+// better rate behind the longer matrix part (64 -> 256 channels, 56 x 56,
+// batch 64: 35.4 us against 38.1).
 //
 // Staging of activations (LDS) follows the folded-scale kernel; see
 // igemm.h.  The weights are read as the 2-bit codes (one 16-byte load per
@@ -65,17 +77,25 @@ constexpr int kStepBytes = 64 * 16;  // codes of one channel tile, one 128-wide 
 // Two workgroups may share a compute unit (at most 256 registers per lane):
 // with two waves per SIMD, one wave's conversions and multiply-adds run
 // while the other waits on its matrix instructions.
-template <int kBits, int kNWO, int kNB, int kCM, int kOut>
-__global__ __launch_bounds__(kThreads, 2) void group_conv_kernel(GroupArgs a) {
+//
+// kNWK = 2: two sets of four waves share the tile's K steps, each with its own
+// activation stages and its loads two steps ahead (see fold_kernel.h); their
+// fp32 partial sums of a block are added once, so no value passes through
+// more roundings than with one set.
+template <int kBits, int kNWO, int kNB, int kCM, int kOut, int kNWK = 1, bool kF8 = kBits == 4>
+__global__ __launch_bounds__(kThreads * kNWK, 2) void group_conv_kernel(GroupArgs a) {
   constexpr int kNWM = 4 / kNWO;
   constexpr int kTO = 32 * kNWO;
   constexpr int kTM = kNWM * kNB * 32;
   using Stager = StagerFor<kBits, kTM, kCM>;
   constexpr int kStage = Stager::kStage;
   constexpr int kLds = 2 * kStage > EpiTile<kOut, kNWO>::kBytes ? 2 * kStage : EpiTile<kOut, kNWO>::kBytes;
-  __shared__ __attribute__((aligned(16))) unsigned char lds[kLds];
+  static_assert(kNWK == 1 || (kNWK == 2 && kNB == 2 && 4 * 16 * 64 * 4 <= kLds), "two sets of four waves");
+  __shared__ __attribute__((aligned(16))) unsigned char lds_all[kNWK * kLds];
 
-  const int tid = threadIdx.x;
+  const int tid = threadIdx.x % kThreads;
+  const int wk = kNWK > 1 ? __builtin_amdgcn_readfirstlane(threadIdx.x / kThreads) : 0;
+  unsigned char* const lds = lds_all + wk * kLds;
   const int lane = tid % 64, wave = tid / 64;
   const int wo = wave % kNWO, wm = wave / kNWO;
   const int tile = xcd_swizzle(blockIdx.x, a.x.n_otiles * a.x.n_mtiles);
@@ -84,8 +104,11 @@ __global__ __launch_bounds__(kThreads, 2) void group_conv_kernel(GroupArgs a) {
 
   const Buf wrs = make_buf(a.codes, a.codes_bytes, kSiteCodes, kBufFlags);
   const Buf ars = make_buf(a.alpha, a.alpha_bytes, kSiteAlpha, kBufFlags);
-  const int nk = (a.x.K + kKT - 1) / kKT;
-  const int wbase = (o0 / 32) * nk * kStepBytes + 16 * lane;
+  const int nk_all = (a.x.K + kKT - 1) / kKT;
+  const int per_set = (nk_all + kNWK - 1) / kNWK;
+  const int ks0 = wk * per_set;  // this wave set's K steps [ks0, nk)
+  const int nk = ks0 + per_set < nk_all ? ks0 + per_set : nk_all;
+  const int wbase = (o0 / 32) * nk_all * kStepBytes + 16 * lane;
   // The group's alphas are the scalar offset, which the buffer range check
   // does not cover: lanes of a channel tile past the padded channel count
   // (O32) take an out-of-range vector offset, which reads zeros, instead of
@@ -95,10 +118,11 @@ __global__ __launch_bounds__(kThreads, 2) void group_conv_kernel(GroupArgs a) {
   // the epilogue's scalars, requested now
   const float sx = *a.sx;
   const float os = out_scale_of<kOut>(a.oscale);
-  ResTile<kOut, kNWO, kNB> res;
+  constexpr int kBlocks = kNB / kNWK;
+  ResTile<kOut, kNWO, kNB, kBlocks> res;
 
   Stager xs;
-  xs.init(a.x, m0, tid);
+  xs.init(a.x, m0, tid, ks0);
 
   // Codes and scales of one step (two groups).  The step is the scalar
   // offset, which the buffer range check does not cover, so a step past the
@@ -131,10 +155,31 @@ __global__ __launch_bounds__(kThreads, 2) void group_conv_kernel(GroupArgs a) {
                          static_cast<int>(0x81818181u), static_cast<int>(0x81818181u)};
   const v16i kZero = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
 
+  // block scales (powers of two, biased by 127) of the uint4 form
+  constexpr int kScale1 = 0x7F7F7F7F, kScale512 = static_cast<int>(0x88888888u);
   auto compute = [&](int stage, const v4i& cw, const float (&al)[2]) {
     const unsigned char* base = lds + stage * kStage;
 #pragma unroll
     for (int blk = 0; blk < 2; ++blk) {
+      if constexpr (kF8) {
+        typedef int v8i __attribute__((ext_vector_type(8)));
+        const v4i wl = expand_ternary_e4m3(static_cast<uint32_t>(cw[2 * blk]));
+        const v4i wh = expand_ternary_e4m3(static_cast<uint32_t>(cw[2 * blk + 1]));
+        const v8i w8 = __builtin_shufflevector(wl, wh, 0, 1, 2, 3, 4, 5, 6, 7);
+#pragma unroll
+        for (int c = 0; c < kNB; ++c) {
+          const v4i xl = *reinterpret_cast<const v4i*>(base + afrag[c][2 * blk]);
+          const v4i xh = *reinterpret_cast<const v4i*>(base + afrag[c][2 * blk + 1]);
+          const v8i x8 = __builtin_shufflevector(xl, xh, 0, 1, 2, 3, 4, 5, 6, 7);
+          v16f p;
+#pragma unroll
+          for (int r = 0; r < 16; ++r) p[r] = 0.0f;
+          p = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(x8, w8, p, 0, 0, 0, kScale512, 0, kScale1);
+#pragma unroll
+          for (int r = 0; r < 16; ++r) acc[c][r] = fmaf(al[blk], p[r], acc[c][r]);
+        }
+        continue;
+      }
       const v4i w[2] = {expand_ternary16(static_cast<uint32_t>(cw[2 * blk])),
                         expand_ternary16(static_cast<uint32_t>(cw[2 * blk + 1]))};
       v4i xf[kNB][2];
@@ -178,12 +223,59 @@ __global__ __launch_bounds__(kThreads, 2) void group_conv_kernel(GroupArgs a) {
   };
   using I0 = std::integral_constant<int, 0>;
   using I1 = std::integral_constant<int, 1>;
-  load_w(I0{}, 0);
+  load_w(I0{}, ks0);
   xs.load(a.x);
-  xs.store(lds, kMask);
-  __syncthreads();
-  int ks = 0;
-  if constexpr (out_res(kOut)) {
+  int ks = ks0;
+  if constexpr (kNWK == 1) {
+    xs.store(lds, kMask);
+    __syncthreads();
+  }
+  if constexpr (kNWK == 2) {
+    Stager xs2 = xs;  // the odd steps' registers
+    xs2.advance(a.x);
+    xs2.load(a.x);
+    load_w(I1{}, ks0 + 1);
+    xs.store(lds, kMask);
+    __syncthreads();
+    auto step2 = [&](auto U, int k, Stager& pub, Stager& req) {
+      constexpr int u = decltype(U)::value;
+      pub.store(lds + (1 - u) * kStage, kMask);  // step k+1
+      req.advance2(a.x);
+      req.load(a.x);                             // step k+2
+      __builtin_amdgcn_sched_barrier(0);
+      if (k < nk) compute(u, cring[u], aring[u]);
+      __builtin_amdgcn_sched_barrier(0);
+      load_w(U, k + 2);
+      __syncthreads();
+    };
+    auto finish = [&](auto U, int k) {
+      constexpr int u = decltype(U)::value;
+      if (a.staged) res.load(a.res, a.x.M, a.x.O, m0, o0 - 32 * wo, tid, wk);
+      __builtin_amdgcn_sched_barrier(0);
+      if (k < nk) compute(u, cring[u], aring[u]);
+    };
+    const int last = ks0 + per_set - 1;  // of either set
+    for (; ks + 2 <= last; ks += 2) {
+      step2(I0{}, ks, xs2, xs);
+      step2(I1{}, ks + 1, xs, xs2);
+    }
+    if (ks < last) {
+      step2(I0{}, ks, xs2, xs);
+      finish(I1{}, ks + 1);
+    } else {
+      finish(I0{}, ks);
+    }
+    // The sets exchange a block each through LDS: set 0 finishes the waves'
+    // first blocks, set 1 the second; set 0's sums come first in both.
+    float* const give = reinterpret_cast<float*>(lds_all + (1 - wk) * kLds) + wave * 16 * 64 + lane;
+    const float* const take = reinterpret_cast<const float*>(lds) + wave * 16 * 64 + lane;
+    __syncthreads();  // fragments read
+#pragma unroll
+    for (int r = 0; r < 16; ++r) give[64 * r] = wk == 0 ? acc[1][r] : acc[0][r];
+    __syncthreads();
+#pragma unroll
+    for (int r = 0; r < 16; ++r) acc[0][r] = (wk == 0 ? acc[0][r] : acc[1][r]) + take[64 * r];
+  } else if constexpr (out_res(kOut)) {
     // The last step prefetches and publishes nothing; the residual is
     // requested before its matrix work.
     auto last = [&](auto U) {
@@ -219,9 +311,9 @@ __global__ __launch_bounds__(kThreads, 2) void group_conv_kernel(GroupArgs a) {
     constexpr bool kR = decltype(rcp)::value;
     auto val = [&](int c, int r) { return acc[c][r] * sx; };
     if (staged)
-      store_staged<kOut, kNWO, kNB, kR>(lds, out, qs, m0, o0 - 32 * wo, wm, wo, tid, res, val);
+      store_staged<kOut, kNWO, kNB, kR, kBlocks>(lds, out, qs, m0, o0 - 32 * wo, wm, wo, tid, res, val, NoNext(), wk);
     else
-      store_direct<kOut, kNB, kR>(out, qs, m0 + wm * kNB * 32, o, lane, val);
+      store_direct<kOut, kBlocks, kR>(out, qs, m0 + wm * kNB * 32 + 32 * wk, o, lane, val);
   });
 }
 
@@ -233,6 +325,27 @@ fgq_status launch_cfg(const GroupArgs& a0, hipStream_t st) {
   a.x.n_mtiles = (a.x.M + kTM - 1) / kTM;
   const int64_t n = static_cast<int64_t>(a.x.n_otiles) * a.x.n_mtiles;
   if (n > 0x7fffffffLL) return FGQ_ERR_SHAPE;
+  // At most one workgroup per compute unit: two wave sets (us, one set ->
+  // two, uint8: 196 tiles of 36 steps 29.6 -> 23.3, of 16 15.7 -> 13.1, of 8
+  // 9.6 -> 8.9; 98 tiles of 4 6.6 -> 6.3).
+  if constexpr (kNWO == 4) {
+    if (a.x.C >= kKT && n <= device_cus() && a.x.K > 3 * kKT) {
+      hipLaunchKernelGGL((group_conv_kernel<kBits, kNWO, kNB, 0, kOut, 2>), dim3(static_cast<uint32_t>(n)),
+                         dim3(2 * kThreads), 0, st, a);
+      return last_launch();
+    }
+  }
+  if constexpr (kBits == 4 && kOut == 0) {
+    if (a.x.K <= kKT) {  // one step
+      if (a.x.C < kKT)
+        hipLaunchKernelGGL((group_conv_kernel<kBits, kNWO, kNB, 1, kOut, 1, false>), dim3(static_cast<uint32_t>(n)),
+                           dim3(kThreads), 0, st, a);
+      else
+        hipLaunchKernelGGL((group_conv_kernel<kBits, kNWO, kNB, 0, kOut, 1, false>), dim3(static_cast<uint32_t>(n)),
+                           dim3(kThreads), 0, st, a);
+      return last_launch();
+    }
+  }
   if (a.x.C < kKT)
     hipLaunchKernelGGL((group_conv_kernel<kBits, kNWO, kNB, 1, kOut>), dim3(static_cast<uint32_t>(n)),
                        dim3(kThreads), 0, st, a);

@@ -92,5 +92,13 @@ __device__ inline v4i expand_ternary16(uint32_t c32) {
   return w;
 }
 
+// The same as e4m3 bytes: table [0, 1.0, 0, -1.0].
+__device__ inline v4i expand_ternary_e4m3(uint32_t c32) {
+  v4i w;
+#pragma unroll
+  for (int i = 0; i < 4; ++i) w[i] = static_cast<int>(__builtin_amdgcn_perm(0u, 0xB8003800u, (c32 >> (2 * i)) & 0x03030303u));
+  return w;
+}
+
 }  // namespace ig
 }  // namespace fgq
