@@ -204,9 +204,8 @@ __device__ inline void store_staged(unsigned char* lds, const OutPtrs& out, cons
             __builtin_nontemporal_store(w, reinterpret_cast<u32x4*>(reinterpret_cast<unsigned char*>(out.y) + byte));
           }
           if constexpr (kCode == 8) {
-            uint32_t cw = 0;
-#pragma unroll
-            for (int i = 0; i < 4; ++i) cw |= qcode<kRcp>(__uint_as_float(w[i]), qs) << (8 * i);
+            const uint32_t cw = qcode4<kRcp>(__uint_as_float(w[0]), __uint_as_float(w[1]), __uint_as_float(w[2]),
+                                             __uint_as_float(w[3]), qs);
             if (check_store(kSiteStoreY, el, 4, n))
               __builtin_nontemporal_store(cw, reinterpret_cast<uint32_t*>(out.q + el));
           } else if constexpr (kCode == 4) {

@@ -198,6 +198,10 @@ fgq_status launch_splitk_reduce(const int32_t* part, int32_t splits, bool dfp, i
 bool wavek_pick(const ConvGeom& g, int kind);
 fgq_status launch_wavek(const uint8_t* q, const float* sx, const void* prepared, int kind, const ConvGeom& g,
                         const LayerOut& out, hipStream_t st);
+// The one-plane layer on images of four 8-bit channels (tinyc.hip).
+bool tinyc_supported(const ConvGeom& g, const uint8_t* q, const LayerOut& out);
+fgq_status launch_tinyc(const uint8_t* q, const float* sx, const void* prepared, const ConvGeom& g,
+                        const LayerOut& out, hipStream_t st);
 // Per-group int8 MFMA kernel with an fp32 alpha epilogue (G = 64).
 bool group_supported(const ConvGeom& g, const uint8_t* q);
 fgq_status launch_group_conv(const uint8_t* q, const float* sx,

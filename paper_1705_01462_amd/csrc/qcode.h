@@ -56,6 +56,30 @@ __device__ inline unsigned qcode(float v, const QScale& c) {
   return static_cast<unsigned>(r);
 }
 
+// Four 8-bit codes as one word, the first in the low byte: the values before
+// the conversion are whole numbers in [0, 255], which v_cvt_pk_u8_f32 turns
+// into a byte in place (conversion, shift and or in one instruction).
+// kBounded: the caller knows that v * y is finite, so the clamp before the
+// correction has nothing to do.
+template <bool kRcp, bool kBounded = false>
+__device__ inline uint32_t qcode4(float v0, float v1, float v2, float v3, const QScale& c) {
+#pragma clang fp contract(off)
+  auto code = [&](float v) {
+    float q;
+    if constexpr (kRcp) {
+      const float q0 = kBounded ? v * c.y : fminf(fmaxf(v * c.y, -16777216.0f), 16777216.0f);
+      q = fmaf(fmaf(-q0, c.s, v), c.y, q0);
+    } else {
+      q = v / c.s;
+    }
+    return fminf(fmaxf(rintf(q), 0.0f), 255.0f);  // NaN -> 0
+  };
+  uint32_t w = __builtin_amdgcn_cvt_pk_u8_f32(code(v0), 0, 0);
+  w = __builtin_amdgcn_cvt_pk_u8_f32(code(v1), 1, w);
+  w = __builtin_amdgcn_cvt_pk_u8_f32(code(v2), 2, w);
+  return __builtin_amdgcn_cvt_pk_u8_f32(code(v3), 3, w);
+}
+
 // f(std::true_type{}) when the scale admits the reciprocal form, else
 // f(std::false_type{}); f passes the flag on to qcode / emit_out.
 template <class F>

@@ -223,7 +223,7 @@ __global__ __launch_bounds__(kThreads) void quantize_coalesced_kernel(
       const int64_t f = f0 + static_cast<int64_t>(i) * kThreads;
       if (f < n4) {
         if constexpr (kBits == 8) {
-          const uint32_t word = code(v[i].x) | (code(v[i].y) << 8) | (code(v[i].z) << 16) | (code(v[i].w) << 24);
+          const uint32_t word = qcode4<decltype(rcp)::value>(v[i].x, v[i].y, v[i].z, v[i].w, qs);
           if (check_store(kSiteStoreQ, 4 * f, 4, n)) __builtin_nontemporal_store(word, reinterpret_cast<uint32_t*>(q) + f);
         } else {
           const uint32_t half = code(v[i].x) | (code(v[i].y) << 4) | (code(v[i].z) << 8) | (code(v[i].w) << 12);

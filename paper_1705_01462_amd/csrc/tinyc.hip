@@ -1,0 +1,333 @@
+// tinyc.hip -- the one-plane layer (8-bit weights, or fixed-point scales) on
+// images of four channels, a network's first layer: the rows of an image are
+// staged once and the matrix instruction's fragments are read from them.
+//
+// The tiled kernel gathers such a layer tap by tap, four 4-byte loads with a
+// bounds test each per 16-deep piece of the reduction, for every output row
+// that uses the tap.  Here a workgroup keeps its channels' weights in
+// registers and walks output rows: per unit (128 output pixels in 4, 2 or 1
+// rows) it copies the input rows they use to LDS as they lie in memory, 4
+// bytes a pixel, out-of-image pixels as zeros, and a wave reads the 16 bytes
+// of four neighbouring taps of a pixel as one fragment piece.  For that the
+// reduction is taken row by row with the row padded to kPR pieces of four taps
+// (zero weights): slice n of 32 holds pieces 2n and 2n + 1.  The weights are
+// gathered from the prepared plane once per workgroup, so its layout is the
+// other kernels'.  The next unit's rows are requested before the current
+// unit's matrix work.
+//
+// Channels are the instruction's rows, so a lane holds four consecutive
+// channels of its pixel; a wave's 32 pixels x 64 channels pass through its own
+// LDS tile (no barrier) and leave as 16-byte pieces of whole pixels.
+//
+// Scales: y = fp32(double(S) * cd), cd = s_x 2^-fl in fp64.  While |S| < 2^24
+// for every input and cd is itself an fp32 value, that is the fp32 product of
+// two fp32 values, rounded once either way, at a third of the instructions.
+//
+// Bound: the codes' vector work (eight instructions an output) beside the
+// output's bytes, 51 MB for a 7x7 layer of 64 channels on 64 images of
+// 224 x 224: 56.9 us gathered tap by tap, 36.5 here.
+#include "fold_kernel.h"
+
+namespace fgq {
+namespace {
+
+using namespace ig;
+
+struct TinyArgs {
+  ActArgs x;
+  const int8_t* planes;
+  const int32_t* bias;
+  const int32_t* fl;
+  const float* sx;
+  const float* oscale;
+  float* y;
+  uint8_t* q;
+  int32_t planes_bytes, nks;
+  int32_t pxw, rows, nseg, nhg, nunits;  // pixel blocks of 32 per row, rows per unit, units per row and image, all
+  int32_t width, prows, words;           // patch: pixels per row, rows, pixels in all
+  int32_t exact24;                       // |S| < 2^24 for every input
+};
+
+// The largest patch of each form, in rows and in 64-pixel pieces of a row (the
+// registers that carry one): 7x7 at stride 2 and 11x11 at stride 4 over a
+// 224- or 227-wide image take 7 x 262 and 15 x 264 pixels.
+constexpr int kRowsOf[4] = {0, 8, 8, 16}, kColsOf[4] = {0, 5, 5, 5};
+
+template <int kPR, int kNS, int kRows, int kCols, int kOut>
+__global__ __launch_bounds__(kThreads, kNS <= 8 ? 3 : 2) void tinyc_kernel(TinyArgs a) {
+  constexpr int kCB = 2;                                         // 32-channel blocks per wave
+  constexpr int kEsz = kOut == 0 ? 32 : kOut;                    // bits per output value
+  constexpr int kRowB = 64 * kEsz / 8;                           // tile bytes per pixel
+  constexpr int kPitch = kRowB + 16;
+  constexpr int kPieces = 32 * kRowB / 16;                       // 16-byte pieces of a wave's tile
+  typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+  struct __attribute__((packed, aligned(4))) Piece { int v[4]; };
+  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+  __shared__ __attribute__((aligned(16))) int sbias[64];
+  unsigned char* const tile = smem + (threadIdx.x / 64) * 32 * kPitch;
+  int* const patch = reinterpret_cast<int*>(smem + 4 * 32 * kPitch);  // two stages of a.words
+
+  const int tid = threadIdx.x, lane = tid % 64, half = lane / 32;
+  const int wave = __builtin_amdgcn_readfirstlane(tid / 64);
+  const int og = blockIdx.y * 64;
+  const int u0 = static_cast<int>(static_cast<int64_t>(blockIdx.x) * a.nunits / gridDim.x);
+  const int u1 = static_cast<int>(static_cast<int64_t>(blockIdx.x + 1) * a.nunits / gridDim.x);
+  if (u0 >= u1) return;
+
+  const Buf xrs = make_buf(a.x.q, a.x.q_bytes, kSiteActs, kBufFlags);
+  struct Unit { int b, ho, wo; };
+  auto unit = [&](int u) {
+    const int seg = u % a.nseg, t = u / a.nseg;
+    return Unit{t / a.nhg, (t % a.nhg) * a.rows, seg * a.pxw * 32};
+  };
+  // Rows of one unit: wave w takes patch rows w, w + 4, ..., a lane the pixels
+  // lane, lane + 64, ... of a row, so a row's bounds are scalar and a pixel's
+  // column is tested once for all rows.
+  constexpr int kLR = (kRows + 3) / 4;  // rows per wave
+  uint32_t ld[kLR][kCols];
+  auto request = [&](int u) {
+    const Unit n = unit(u);
+    const int hi0 = n.ho * a.x.sh - a.x.ph, wi0 = n.wo * a.x.sw - a.x.pw;
+    uint32_t voff[kCols];
+#pragma unroll
+    for (int j = 0; j < kCols; ++j) {
+      const int c = lane + 64 * j, wi = wi0 + c;
+      const bool ok = (c < a.width) & (static_cast<unsigned>(wi) < static_cast<unsigned>(a.x.W));
+      voff[j] = ok ? static_cast<uint32_t>(4 * wi) : kOutOfRange;
+    }
+#pragma unroll
+    for (int i = 0; i < kLR; ++i) {
+      const int r = wave + 4 * i, hi = hi0 + r;
+      const bool ok = r < a.prows && static_cast<unsigned>(hi) < static_cast<unsigned>(a.x.H);
+      const int soff = ok ? (n.b * a.x.H + hi) * a.x.W * 4 : 0;
+#pragma unroll
+      for (int j = 0; j < kCols; ++j) ld[i][j] = ok ? buf_load_b32(xrs, voff[j], soff) : 0u;
+    }
+  };
+  auto publish = [&](int stage) {
+#pragma unroll
+    for (int i = 0; i < kLR; ++i) {
+      const int r = wave + 4 * i;
+      if (r < a.prows) {
+#pragma unroll
+        for (int j = 0; j < kCols; ++j) {
+          const int c = lane + 64 * j;
+          if (c < a.width) patch[stage * a.words + r * a.width + c] = static_cast<int>(ld[i][j] ^ 0x80808080u);  // q - 128
+        }
+      }
+    }
+  };
+  request(u0);
+
+  const float sx = *a.sx;
+  const float os = out_scale_of<kOut>(a.oscale);
+  const int32_t fl = *a.fl;
+
+  // ---- weights: slice n, piece p = 2n + half is taps s = 4 (p % kPR) + [0, 4)
+  // of filter row p / kPR
+  const Buf wrs = make_buf(a.planes, a.planes_bytes, kSitePlanes, kBufFlags);
+  v4i w[kCB][kNS];
+#pragma unroll
+  for (int cb = 0; cb < kCB; ++cb) {
+    const int o = og + 32 * cb + lane % 32;
+#pragma unroll
+    for (int n = 0; n < kNS; ++n) {
+      const int r = half ? (2 * n + 1) / kPR : 2 * n / kPR;
+      const int s0 = 4 * (half ? (2 * n + 1) % kPR : 2 * n % kPR);
+#pragma unroll
+      for (int t = 0; t < 4; ++t) {
+        const int k = (r * a.x.S + s0 + t) * 4;
+        const bool ok = (o < a.x.O) & (r < a.x.R) & (s0 + t < a.x.S);
+        const uint32_t off = static_cast<uint32_t>((((o / 32) * a.nks + k / 64) * 2 + (k % 64) / 32) * 1024 +
+                                                   (o % 32 + 32 * ((k % 32) / 16)) * 16 + k % 16);
+        w[cb][n][t] = static_cast<int>(buf_load_b32(wrs, ok ? off : kOutOfRange, 0));
+      }
+    }
+  }
+  if (tid < 64) sbias[tid] = og + tid < a.x.O ? a.bias[og + tid] : 0;
+
+  // ---- the wave's pixels: row wave / pxw of the unit, block wave % pxw
+  const int prow = wave / a.pxw, pblk = wave % a.pxw;
+  int foff[kNS];  // word of this lane's piece of slice n (rows past the filter: the last, on zero weights)
+#pragma unroll
+  for (int n = 0; n < kNS; ++n) {
+    const int r = half ? (2 * n + 1) / kPR : 2 * n / kPR;
+    const int s0 = 4 * (half ? (2 * n + 1) % kPR : 2 * n % kPR);
+    foff[n] = (prow * a.x.sh + (r < a.x.R ? r : a.x.R - 1)) * a.width + (32 * pblk + lane % 32) * a.x.sw + s0;
+  }
+
+  const double cd = fl > -2048 && fl < 2048 ? static_cast<double>(sx) * ldexp(1.0, -fl) : 0.0;
+  const float cf = static_cast<float>(cd);
+  // (the code's v * y stays finite too: |v| < 2^24 cf, y = 1 / os)
+  const bool fast = a.exact24 && static_cast<double>(cf) == cd && (kOut == 0 || cf * 16777216.0f / os < __builtin_huge_valf());
+  publish(0);
+  __syncthreads();
+
+  for (int u = u0; u < u1; ++u) {
+    const int stage = (u - u0) & 1;
+    if (u + 1 < u1) request(u + 1);
+    const Unit n = unit(u);
+    const int* const src = patch + stage * a.words;
+
+    v16i acc[kCB];
+#pragma unroll
+    for (int cb = 0; cb < kCB; ++cb)
+#pragma unroll
+      for (int qd = 0; qd < 4; ++qd) {
+        const v4i b = *reinterpret_cast<const v4i*>(&sbias[32 * cb + 8 * qd + 4 * half]);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) acc[cb][4 * qd + i] = b[i];
+      }
+#pragma unroll
+    for (int s = 0; s < kNS; ++s) {
+      const Piece p = *reinterpret_cast<const Piece*>(src + foff[s]);
+      const v4i xf = {p.v[0], p.v[1], p.v[2], p.v[3]};
+#pragma unroll
+      for (int cb = 0; cb < kCB; ++cb) acc[cb] = __builtin_amdgcn_mfma_i32_32x32x32_i8(w[cb][s], xf, acc[cb], 0, 0, 0);
+    }
+
+    // ---- lane: pixel lane % 32, channels 32 cb + 8 qd + 4 half + [0, 4)
+    const int ho = n.ho + prow, wo0 = n.wo + 32 * pblk;
+    with_out_scale<kOut>(os, [&](const QScale& qs, auto rcp) {
+      constexpr bool kR = decltype(rcp)::value;
+      auto fill = [&](auto F) {
+#pragma unroll
+        for (int cb = 0; cb < kCB; ++cb)
+#pragma unroll
+          for (int qd = 0; qd < 4; ++qd) {
+            float v[4];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+              const int S = acc[cb][4 * qd + i];
+              v[i] = decltype(F)::value ? static_cast<float>(S) * cf : static_cast<float>(static_cast<double>(S) * cd);
+            }
+            unsigned char* const dst = tile + (lane % 32) * kPitch + (32 * cb + 8 * qd + 4 * half) * kEsz / 8;
+            if constexpr (kOut == 0) {
+              *reinterpret_cast<u32x4*>(dst) = u32x4{__float_as_uint(v[0]), __float_as_uint(v[1]), __float_as_uint(v[2]),
+                                                     __float_as_uint(v[3])};
+            } else {
+              if constexpr (kOut == 8) {
+                *reinterpret_cast<uint32_t*>(dst) = qcode4<kR, decltype(F)::value>(v[0], v[1], v[2], v[3], qs);
+              } else {
+                uint32_t c = 0;
+#pragma unroll
+                for (int i = 0; i < 4; ++i) c |= qcode<kR>(v[i], qs) << (4 * i);
+                *reinterpret_cast<uint16_t*>(dst) = static_cast<uint16_t>(c);
+              }
+            }
+          }
+      };
+      if (fast)
+        fill(std::true_type{});
+      else
+        fill(std::false_type{});
+    });
+    if (ho < a.x.Ho) {
+      const int64_t e0 = (static_cast<int64_t>(n.b * a.x.Ho + ho) * a.x.Wo + wo0) * a.x.O + og;
+      const int64_t nbytes = static_cast<int64_t>(a.x.M) * a.x.O * kEsz / 8;
+      unsigned char* const out = kOut == 0 ? reinterpret_cast<unsigned char*>(a.y) : a.q;
+#pragma unroll
+      for (int t0 = 0; t0 < kPieces; t0 += 64) {
+        const int t = t0 + lane;
+        const int px = t / (kRowB / 16), piece = t % (kRowB / 16);
+        if (wo0 + px < a.x.Wo && og + piece * (128 / kEsz) < a.x.O) {
+          const u32x4 v = *reinterpret_cast<const u32x4*>(tile + px * kPitch + 16 * piece);
+          const int64_t byte = (e0 + static_cast<int64_t>(px) * a.x.O) * kEsz / 8 + 16 * piece;
+          if (check_store(kSiteStoreY, byte, 16, nbytes))
+            __builtin_nontemporal_store(v, reinterpret_cast<u32x4*>(out + byte));
+        }
+      }
+    }
+    if (u + 1 < u1) publish(1 - stage);
+    __syncthreads();
+  }
+}
+
+template <int kPR, int kNS, int kRows, int kCols, int kOut>
+fgq_status launch(const TinyArgs& a, hipStream_t st) {
+  constexpr int kTiles = 4 * 32 * (64 * (kOut == 0 ? 32 : kOut) / 8 + 16);
+  const int64_t ogs = ceil_div(a.x.O, 64);
+  // as many workgroups as fit at once, each walking a run of units (their
+  // rows overlap), the same number for every 64 channels
+  const int64_t fit = (kNS <= 8 ? 3LL : 2LL) * device_cus();
+  const int64_t gx = std::max<int64_t>(1, std::min<int64_t>(a.nunits, fit / ogs));
+  hipLaunchKernelGGL((tinyc_kernel<kPR, kNS, kRows, kCols, kOut>), dim3(static_cast<uint32_t>(gx), static_cast<uint32_t>(ogs)),
+                     dim3(kThreads), kTiles + 8 * a.words, st, a);
+  return last_launch();
+}
+
+template <int kOut>
+fgq_status launch_form(int form, const TinyArgs& a, hipStream_t st) {
+  switch (form) {
+    case 1: return launch<1, 2, kRowsOf[1], kColsOf[1], kOut>(a, st);
+    case 2: return launch<2, 7, kRowsOf[2], kColsOf[2], kOut>(a, st);
+    default: return launch<3, 17, kRowsOf[3], kColsOf[3], kOut>(a, st);
+  }
+}
+
+// Filter rows of up to 4, 8 or 12 taps (1, 2 or 3 pieces), as many of them as
+// the form's slices hold; 0: none of the forms.
+int tinyc_form(const ConvGeom& g) {
+  if (g.S <= 4 && g.R <= 4) return 1;
+  if (g.S <= 8 && g.R <= 7) return 2;
+  if (g.S <= 12 && g.R <= 11) return 3;
+  return 0;
+}
+
+void tinyc_patch(const ConvGeom& g, int form, TinyArgs* a) {
+  a->pxw = g.Wo <= 32 ? 1 : (g.Wo <= 64 ? 2 : 4);
+  a->rows = 4 / a->pxw;
+  a->width = static_cast<int32_t>((a->pxw * 32 - 1) * g.sw + 4 * form);
+  a->prows = static_cast<int32_t>((a->rows - 1) * g.sh + g.R);
+  a->words = a->width * a->prows;
+}
+
+}  // namespace
+
+// Taken where its form fits: four 8-bit channels, outputs in whole aligned
+// 16-byte pieces, a patch within the registers that carry it.  Other first
+// layers (eight channels, 4-bit, three planes, residuals) stay with the tiled
+// kernel.
+bool tinyc_supported(const ConvGeom& g, const uint8_t* q, const LayerOut& out) {
+  if (g.C != 4 || g.bits != 8 || (out.bits != 0 && out.bits != 8 && out.bits != 4)) return false;
+  const int form = tinyc_form(g);
+  if (form == 0 || g.sh > 64 || g.sw > 64 || reinterpret_cast<uintptr_t>(q) % 4 != 0) return false;
+  TinyArgs a;
+  tinyc_patch(g, form, &a);
+  if (a.prows > kRowsOf[form] || a.width > 64 * kColsOf[form]) return false;
+  const int per = out.bits == 0 ? 4 : 128 / out.bits;
+  const void* p = out.bits == 0 ? static_cast<const void*>(out.y) : out.q;
+  if (g.O % per != 0 || reinterpret_cast<uintptr_t>(p) % 16 != 0) return false;
+  const int64_t units = g.B * ceil_div(g.Ho, a.rows) * ceil_div(g.Wo, 32 * a.pxw);
+  return units < (1LL << 31) && ceil_div(g.O, 64) <= device_cus();
+}
+
+fgq_status launch_tinyc(const uint8_t* q, const float* sx, const void* prepared, const ConvGeom& g,
+                        const LayerOut& out, hipStream_t st) {
+  const PreparedLayout L = prepared_layout_dfp(g.O, g.K, g.G);
+  const char* base = static_cast<const char*>(prepared);
+  const int form = tinyc_form(g);
+  TinyArgs a;
+  fill_act_args(g, q, &a.x);
+  a.planes = reinterpret_cast<const int8_t*>(base + L.planes_off);
+  a.bias = reinterpret_cast<const int32_t*>(base + L.bias_off);
+  a.fl = reinterpret_cast<const int32_t*>(base);
+  a.sx = sx;
+  a.oscale = out.scale;
+  a.y = out.y;
+  a.q = out.q;
+  a.planes_bytes = static_cast<int32_t>(L.O32 * L.Kp);
+  a.nks = static_cast<int32_t>(L.nks);
+  tinyc_patch(g, form, &a);
+  a.nseg = static_cast<int32_t>(ceil_div(g.Wo, 32 * a.pxw));
+  a.nhg = static_cast<int32_t>(ceil_div(g.Ho, a.rows));
+  a.nunits = static_cast<int32_t>(g.B * a.nhg * a.nseg);
+  a.exact24 = 255 * 128 * g.K < (1 << 24);  // codes up to 255, weights of at most 128
+  switch (out.bits) {
+    case 0: return launch_form<0>(form, a, st);
+    case 8: return launch_form<8>(form, a, st);
+    default: return launch_form<4>(form, a, st);
+  }
+}
+
+}  // namespace fgq

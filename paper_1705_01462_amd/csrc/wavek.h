@@ -334,9 +334,7 @@ __global__ __launch_bounds__(64 * kWO * kWK, 2) void wavek_kernel(WavekArgs a) {
         }
       }
       if (a.code_bits == 8) {
-        uint32_t cw = 0;
-#pragma unroll
-        for (int c = 0; c < 4; ++c) cw |= qcode<kR>(v[c], qs) << (8 * c);
+        const uint32_t cw = qcode4<kR>(v[0], v[1], v[2], v[3], qs);
         if (vec) {
           if (check_store(kSiteStoreY, e, 4, n)) __builtin_nontemporal_store(cw, reinterpret_cast<uint32_t*>(a.q + e));
         } else {
