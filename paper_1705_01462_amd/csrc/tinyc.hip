@@ -19,13 +19,14 @@
 // channels of its pixel; a wave's 32 pixels x 64 channels pass through its own
 // LDS tile (no barrier) and leave as 16-byte pieces of whole pixels.
 //
-// Scales: y = fp32(double(S) * cd), cd = s_x 2^-fl in fp64.  While |S| < 2^24
-// for every input and cd is itself an fp32 value, that is the fp32 product of
-// two fp32 values, rounded once either way, at a third of the instructions.
+// Scales: y = fp32(double(S) * cd), cd = s_x 2^-fl in fp64.  |S| <= 255 * 128 *
+// 224 < 2^24 here, so while cd is itself an fp32 value, that is the fp32
+// product of two fp32 values, rounded once either way, at a third of the
+// instructions.
 //
 // Bound: the codes' vector work (eight instructions an output) beside the
 // output's bytes, 51 MB for a 7x7 layer of 64 channels on 64 images of
-// 224 x 224: 56.9 us gathered tap by tap, 36.5 here.
+// 224 x 224: 56.9 us gathered tap by tap, 33.2 here.
 #include "fold_kernel.h"
 
 namespace fgq {
@@ -45,16 +46,14 @@ struct TinyArgs {
   int32_t planes_bytes, nks;
   int32_t pxw, rows, nseg, nhg, nunits;  // pixel blocks of 32 per row, rows per unit, units per row and image, all
   int32_t width, prows, words;           // patch: pixels per row, rows, pixels in all
-  int32_t exact24;                       // |S| < 2^24 for every input
 };
 
-// The largest patch of each form, in rows and in 64-pixel pieces of a row (the
-// registers that carry one): 7x7 at stride 2 and 11x11 at stride 4 over a
-// 224- or 227-wide image take 7 x 262 and 15 x 264 pixels.
-constexpr int kRowsOf[4] = {0, 8, 8, 16}, kColsOf[4] = {0, 5, 5, 5};
+// The largest patch, in rows and in 64-pixel pieces of a row (the registers
+// that carry one): 7x7 at stride 2 over a 224-wide image takes 7 x 262 pixels.
+constexpr int kRows = 8, kCols = 5;
 
-template <int kPR, int kNS, int kRows, int kCols, int kOut>
-__global__ __launch_bounds__(kThreads, kNS <= 8 ? 3 : 2) void tinyc_kernel(TinyArgs a) {
+template <int kPR, int kNS, int kOut>
+__global__ __launch_bounds__(kThreads, 3) void tinyc_kernel(TinyArgs a) {
   constexpr int kCB = 2;                                         // 32-channel blocks per wave
   constexpr int kEsz = kOut == 0 ? 32 : kOut;                    // bits per output value
   constexpr int kRowB = 64 * kEsz / 8;                           // tile bytes per pixel
@@ -123,24 +122,37 @@ __global__ __launch_bounds__(kThreads, kNS <= 8 ? 3 : 2) void tinyc_kernel(TinyA
   const float os = out_scale_of<kOut>(a.oscale);
   const int32_t fl = *a.fl;
 
-  // ---- weights: slice n, piece p = 2n + half is taps s = 4 (p % kPR) + [0, 4)
-  // of filter row p / kPR
+  // ---- weights: the channels' part of the plane through LDS as it lies in
+  // memory (two channel tiles of Kp x 32 bytes), then this lane's pieces of
+  // it: slice n, piece p = 2n + half is taps s = 4 (p % kPR) + [0, 4) of
+  // filter row p / kPR.  (Gathered from memory tap by tap, 56 loads a lane
+  // with their addresses took 12 us of the launch.)
   const Buf wrs = make_buf(a.planes, a.planes_bytes, kSitePlanes, kBufFlags);
+  const int tileb = a.nks * 2048;  // bytes of one channel tile
+  for (int t = 16 * tid; t < kCB * tileb; t += 16 * kThreads)
+    *reinterpret_cast<v4i*>(smem + t) = buf_load_b128(wrs, (og / 32) * tileb + t, 0);
+  __syncthreads();
   v4i w[kCB][kNS];
 #pragma unroll
-  for (int cb = 0; cb < kCB; ++cb) {
-    const int o = og + 32 * cb + lane % 32;
+  for (int n = 0; n < kNS; ++n) {
 #pragma unroll
-    for (int n = 0; n < kNS; ++n) {
-      const int r = half ? (2 * n + 1) / kPR : 2 * n / kPR;
-      const int s0 = 4 * (half ? (2 * n + 1) % kPR : 2 * n % kPR);
+    for (int t = 0; t < 4; ++t) {
+      // the tap's place in a channel tile, for either half of the wave
+      int at[2];
+      bool in[2];
 #pragma unroll
-      for (int t = 0; t < 4; ++t) {
-        const int k = (r * a.x.S + s0 + t) * 4;
-        const bool ok = (o < a.x.O) & (r < a.x.R) & (s0 + t < a.x.S);
-        const uint32_t off = static_cast<uint32_t>((((o / 32) * a.nks + k / 64) * 2 + (k % 64) / 32) * 1024 +
-                                                   (o % 32 + 32 * ((k % 32) / 16)) * 16 + k % 16);
-        w[cb][n][t] = static_cast<int>(buf_load_b32(wrs, ok ? off : kOutOfRange, 0));
+      for (int h = 0; h < 2; ++h) {
+        const int r = (2 * n + h) / kPR, s = 4 * ((2 * n + h) % kPR) + t;
+        const int k = (r * a.x.S + s) * 4;
+        in[h] = r < a.x.R && s < a.x.S;
+        at[h] = in[h] ? (k / 32) * 1024 + ((k % 32) / 16) * 512 + k % 16 : 0;
+      }
+      const int off = (half ? at[1] : at[0]) + (lane % 32) * 16;
+      const bool ok = half ? in[1] : in[0];
+#pragma unroll
+      for (int cb = 0; cb < kCB; ++cb) {
+        const int v = *reinterpret_cast<const int*>(smem + cb * tileb + off);
+        w[cb][n][t] = ok ? v : 0;
       }
     }
   }
@@ -159,7 +171,8 @@ __global__ __launch_bounds__(kThreads, kNS <= 8 ? 3 : 2) void tinyc_kernel(TinyA
   const double cd = fl > -2048 && fl < 2048 ? static_cast<double>(sx) * ldexp(1.0, -fl) : 0.0;
   const float cf = static_cast<float>(cd);
   // (the code's v * y stays finite too: |v| < 2^24 cf, y = 1 / os)
-  const bool fast = a.exact24 && static_cast<double>(cf) == cd && (kOut == 0 || cf * 16777216.0f / os < __builtin_huge_valf());
+  const bool fast = static_cast<double>(cf) == cd && (kOut == 0 || cf * 16777216.0f / os < __builtin_huge_valf());
+  __syncthreads();  // the weights are read; the patches take their place
   publish(0);
   __syncthreads();
 
@@ -243,35 +256,32 @@ __global__ __launch_bounds__(kThreads, kNS <= 8 ? 3 : 2) void tinyc_kernel(TinyA
   }
 }
 
-template <int kPR, int kNS, int kRows, int kCols, int kOut>
+template <int kPR, int kNS, int kOut>
 fgq_status launch(const TinyArgs& a, hipStream_t st) {
   constexpr int kTiles = 4 * 32 * (64 * (kOut == 0 ? 32 : kOut) / 8 + 16);
   const int64_t ogs = ceil_div(a.x.O, 64);
   // as many workgroups as fit at once, each walking a run of units (their
   // rows overlap), the same number for every 64 channels
-  const int64_t fit = (kNS <= 8 ? 3LL : 2LL) * device_cus();
+  const int64_t fit = 3LL * device_cus();
   const int64_t gx = std::max<int64_t>(1, std::min<int64_t>(a.nunits, fit / ogs));
-  hipLaunchKernelGGL((tinyc_kernel<kPR, kNS, kRows, kCols, kOut>), dim3(static_cast<uint32_t>(gx), static_cast<uint32_t>(ogs)),
-                     dim3(kThreads), kTiles + 8 * a.words, st, a);
+  hipLaunchKernelGGL((tinyc_kernel<kPR, kNS, kOut>), dim3(static_cast<uint32_t>(gx), static_cast<uint32_t>(ogs)),
+                     dim3(kThreads), std::max(kTiles + 8 * a.words, 2 * a.nks * 2048), st, a);
   return last_launch();
+}
+
+// Filter rows of up to 4 or 8 taps (1 or 2 pieces), as many of them as the
+// form's slices hold; 0: neither.  11x11 filters (three pieces, 17 slices)
+// stay with the tiled kernel: their weights fill the registers, 35 us there
+// against 48 on 64 images of 224 x 224.
+int tinyc_form(const ConvGeom& g) {
+  if (g.S <= 4 && g.R <= 4) return 1;
+  if (g.S <= 8 && g.R <= 7) return 2;
+  return 0;
 }
 
 template <int kOut>
 fgq_status launch_form(int form, const TinyArgs& a, hipStream_t st) {
-  switch (form) {
-    case 1: return launch<1, 2, kRowsOf[1], kColsOf[1], kOut>(a, st);
-    case 2: return launch<2, 7, kRowsOf[2], kColsOf[2], kOut>(a, st);
-    default: return launch<3, 17, kRowsOf[3], kColsOf[3], kOut>(a, st);
-  }
-}
-
-// Filter rows of up to 4, 8 or 12 taps (1, 2 or 3 pieces), as many of them as
-// the form's slices hold; 0: none of the forms.
-int tinyc_form(const ConvGeom& g) {
-  if (g.S <= 4 && g.R <= 4) return 1;
-  if (g.S <= 8 && g.R <= 7) return 2;
-  if (g.S <= 12 && g.R <= 11) return 3;
-  return 0;
+  return form == 1 ? launch<1, 2, kOut>(a, st) : launch<2, 7, kOut>(a, st);
 }
 
 void tinyc_patch(const ConvGeom& g, int form, TinyArgs* a) {
@@ -294,12 +304,17 @@ bool tinyc_supported(const ConvGeom& g, const uint8_t* q, const LayerOut& out) {
   if (form == 0 || g.sh > 64 || g.sw > 64 || reinterpret_cast<uintptr_t>(q) % 4 != 0) return false;
   TinyArgs a;
   tinyc_patch(g, form, &a);
-  if (a.prows > kRowsOf[form] || a.width > 64 * kColsOf[form]) return false;
+  if (a.prows > kRows || a.width > 64 * kCols) return false;
   const int per = out.bits == 0 ? 4 : 128 / out.bits;
   const void* p = out.bits == 0 ? static_cast<const void*>(out.y) : out.q;
   if (g.O % per != 0 || reinterpret_cast<uintptr_t>(p) % 16 != 0) return false;
-  const int64_t units = g.B * ceil_div(g.Ho, a.rows) * ceil_div(g.Wo, 32 * a.pxw);
-  return units < (1LL << 31) && ceil_div(g.O, 64) <= device_cus();
+  const int64_t segs = ceil_div(g.Wo, 32 * a.pxw), units = g.B * ceil_div(g.Ho, a.rows) * segs;
+  if (units >= (1LL << 31) || ceil_div(g.O, 64) > device_cus()) return false;
+  // 7x7 (us, tiled -> here, codes out): rows that fill their units gain at
+  // every batch (112 pixels: 1 image 7.4 -> 7.0, 8 13.4 -> 12.5, 64 60 -> 35);
+  // 80 pixels in units of 128 only once there are several units per
+  // workgroup (640 units 9.6 -> 10.8, 1280 13.7 -> 13.5, 2560 21.9 -> 18.7).
+  return form == 1 || 8 * g.Wo >= 7 * 32 * a.pxw * segs || units > 5 * device_cus();
 }
 
 fgq_status launch_tinyc(const uint8_t* q, const float* sx, const void* prepared, const ConvGeom& g,
@@ -322,7 +337,6 @@ fgq_status launch_tinyc(const uint8_t* q, const float* sx, const void* prepared,
   a.nseg = static_cast<int32_t>(ceil_div(g.Wo, 32 * a.pxw));
   a.nhg = static_cast<int32_t>(ceil_div(g.Ho, a.rows));
   a.nunits = static_cast<int32_t>(g.B * a.nhg * a.nseg);
-  a.exact24 = 255 * 128 * g.K < (1 << 24);  // codes up to 255, weights of at most 128
   switch (out.bits) {
     case 0: return launch_form<0>(form, a, st);
     case 8: return launch_form<8>(form, a, st);

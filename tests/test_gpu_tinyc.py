@@ -1,7 +1,7 @@
 """The first layer on four-channel 8-bit images: 8-bit weights and fixed-point
 scales, bit for bit against the oracle.  Output widths on both sides of a
 unit's 32, 64 and 128 pixels, rows that end inside a unit, filters that fill
-their form's pieces and that do not, sums past 2^24 (the fp64 scaling), output
+their form's pieces and that do not, a scale outside fp32 (the fp64 scaling), output
 channels that are not whole tiles, fp32, 8- and 4-bit outputs, and outputs the
 form refuses (the tiled kernel).  Images hold 0 and 255 at their borders."""
 import numpy as np
@@ -30,7 +30,9 @@ CASES = [
     (1, 13, 33, 16, 4, 4, (1, 3), (2, 0)),
     (1, 11, 40, 80, 5, 5, (1, 1), (2, 2)),
     (2, 51, 63, 96, 11, 11, (4, 4), (0, 0)),
-    (1, 30, 70, 32, 11, 12, (2, 1), (5, 6)),    # K = 528: sums past 2^24
+    (1, 30, 70, 32, 11, 12, (2, 1), (5, 6)),    # no form
+    (2, 30, 250, 64, 7, 7, (2, 2), (3, 3)),     # 125 wide: a full unit
+    (40, 21, 9, 48, 7, 8, (1, 2), (3, 4)),      # many images, units mostly empty
     (1, 16, 20, 100, 7, 7, (2, 2), (3, 3)),     # whole fp32 pieces, no whole code pieces
     (1, 16, 20, 34, 3, 3, (1, 1), (1, 1)),      # neither
     (1, 40, 20, 32, 13, 13, (1, 1), (6, 6)),    # no form
@@ -66,7 +68,7 @@ def test_w8(case):
                                           b, so), ref, O, "w8")
 
 
-@pytest.mark.parametrize("case", CASES[:2] + CASES[6:8])
+@pytest.mark.parametrize("case", CASES[:2] + CASES[8:9])
 def test_fixed_point(case):
     B, H, W, O, R, S, st, pad = case
     w = fi.he_weights(O, 4, R, S, "tinyc")
