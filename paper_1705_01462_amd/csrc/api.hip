@@ -195,15 +195,24 @@ int64_t fgq_group_count(int64_t O, int64_t K, int32_t G) {
 
 namespace {
 
-// Wait for the offline step, then report non-finite weights (their groups
-// carry alpha = NaN, gathered into alpha[0] on the device).
-fgq_status ternarize_finish(float* alpha, int64_t ng, hipStream_t st) {
-  const fgq_status rc = launch_alpha_nan(alpha, ng, st);
+// Runs the offline step, waits for it, then reports non-finite weights (their
+// groups carry alpha = NaN, gathered into alpha[0] on the device; a failing
+// layer runs again, so that only those groups keep it).
+fgq_status ternarize_finish(const float* w, int64_t O, int64_t C, int32_t R, int32_t S, int32_t G, int32_t method,
+                            uint8_t* codes, float* alpha, float* delta, float* delta_n, hipStream_t st) {
+  const int64_t ng = O * (static_cast<int64_t>(R) * S * C / G);
+  auto run = [&] { return launch_ternarize(w, O, C, R, S, G, method, codes, alpha, delta, delta_n, st); };
+  fgq_status rc = run();
+  if (rc == FGQ_OK) rc = launch_alpha_nan(alpha, ng, st);
   if (rc != FGQ_OK) return rc;
   float first = 0.0f;
   FGQ_TRY_HIP(hipMemcpyAsync(&first, alpha, sizeof(first), hipMemcpyDeviceToHost, st));
   FGQ_TRY_HIP(hipStreamSynchronize(st));
-  return first != first ? FGQ_ERR_NONFINITE : FGQ_OK;
+  if (first == first) return FGQ_OK;
+  rc = run();
+  if (rc != FGQ_OK) return rc;
+  FGQ_TRY_HIP(hipStreamSynchronize(st));
+  return FGQ_ERR_NONFINITE;
 }
 
 }  // namespace
@@ -229,9 +238,7 @@ fgq_status fgq_ternarize(const float* w, int64_t O, int64_t C, int32_t R, int32_
     FGQ_TRY_HIP(hipStreamSynchronize(st));
     method = pick;
   }
-  fgq_status rc = launch_ternarize(w, O, C, R, S, G, method, codes, alpha, delta, nullptr, st);
-  if (rc != FGQ_OK) return rc;
-  return ternarize_finish(alpha, O * (K / G), st);
+  return ternarize_finish(w, O, C, R, S, G, method, codes, alpha, delta, nullptr, st);
 }
 
 fgq_status fgq_ternarize_asym(const float* w, int64_t O, int64_t C, int32_t R, int32_t S, int32_t G,
@@ -239,11 +246,7 @@ fgq_status fgq_ternarize_asym(const float* w, int64_t O, int64_t C, int32_t R, i
   if (!w || !codes || !alpha) return FGQ_ERR_NULL;
   if (O < 1 || C < 1 || R < 1 || S < 1) return FGQ_ERR_SHAPE;
   if (G < 1 || C % G != 0) return FGQ_ERR_GROUP;
-  const int64_t K = static_cast<int64_t>(R) * S * C;
-  hipStream_t st = as_stream(stream);
-  fgq_status rc = launch_ternarize(w, O, C, R, S, G, kTernAsym, codes, alpha, delta_p, delta_n, st);
-  if (rc != FGQ_OK) return rc;
-  return ternarize_finish(alpha, O * (K / G), st);
+  return ternarize_finish(w, O, C, R, S, G, kTernAsym, codes, alpha, delta_p, delta_n, as_stream(stream));
 }
 
 fgq_status fgq_ks_distances(const float* w, int64_t n, double* d, void* stream) {

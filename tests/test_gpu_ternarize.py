@@ -48,3 +48,17 @@ def test_nonfinite_anywhere(where, G):
         with pytest.raises(fgq.FgqError) as e:
             fgq.fgq_ternarize(torch.from_numpy(w).cuda(), G)
         assert e.value.code == 5
+
+
+def test_nonfinite_marks_its_groups_only():
+    w = fi.he_weights(16, 64, 3, 3, "tern-nan-groups")
+    w[5, 33, 1, 1] = np.nan
+    d = torch.from_numpy(w).cuda()
+    O, K, G = 16, 576, 4
+    codes = torch.empty((O, K // 4), dtype=torch.uint8, device="cuda")
+    alpha = torch.empty((O, K // G), device="cuda")
+    rc = fgq.lib().fgq_ternarize(d.data_ptr(), O, 64, 3, 3, G, fgq.FGQ_TERN_EXACT, codes.data_ptr(), alpha.data_ptr(),
+                                 None, torch.cuda.current_stream().cuda_stream)
+    assert rc == 5
+    bad = torch.isnan(alpha).nonzero().tolist()
+    assert bad == [[5, (4 * 64 + 33) // G]]  # tap (1, 1) is the fifth
