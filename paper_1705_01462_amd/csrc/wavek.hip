@@ -23,9 +23,6 @@ namespace fgq {
 // kernel.
 bool wavek_pick(const ConvGeom& g, int kind) {
   if (g.C % 16 != 0) return false;  // other C: a fragment's 16 k are not one run of channels
-  // Longer reductions (groups of 64 alone have them): the reciprocals that
-  // split k into tap and channel are exact below 65536 only.
-  if (g.K > kFoldMaxK) return false;
   const int64_t nk = ceil_div(g.K, 128);
   const int64_t wgs = ceil_div(g.M, 32) * ceil_div(g.O, 32 * wavek_channel_waves(static_cast<int>(nk)));
   const int64_t cus = ig::device_cus();

@@ -134,20 +134,3 @@ def test_one_unaligned_output():
 ])
 def test_fixed_point_two_sets(case, bits):
     test_fixed_point(case, bits)
-
-
-def test_long_reduction():
-    # groups of 64 take reductions past 65536 (the tiled kernel): only the last
-    # group's activations are nonzero, so a tap or channel split that is off by
-    # one near K's end shows
-    K, O, G, M = 524224, 33, 64, 3
-    w = fi.he_weights(O, K, 1, 1, "wavek-long")
-    t, a, _ = oracle.ternarize(w, G)
-    codes = oracle.pack_codes(t)
-    q = np.zeros((M, K), np.uint8)
-    q[:, -64:] = fi.rng("wavek-long-q").integers(1, 256, (M, 64))
-    s = np.float32(0.01)
-    prep = fgq.fgq_prepare_weights(dev(codes), dev(a), O, K, G)
-    y = fgq.fgq_gemm(dev(q.reshape(-1)), 8, dev(np.array([s])), M, K, dev(codes), dev(a), O, G, prepared=prep)
-    ref, mag = oracle.conv2d_rows(q.reshape(-1), 8, s, (1, M, 1, K), codes, a, O, 1, 1, (1, 1), (0, 0), G, np.arange(M))
-    assert np.all(np.abs(y.view(M, O).cpu().numpy().astype(np.float64) - ref) <= 1e-5 * mag)
