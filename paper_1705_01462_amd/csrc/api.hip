@@ -519,6 +519,7 @@ fgq_status fgq_gemm_ws(const uint8_t* q, int32_t bits, const float* sx, int64_t 
     const bool ws_ok = ws && reinterpret_cast<uintptr_t>(ws) % 4 == 0 && ws_bytes >= fgq_gemm_ws_bytes(M, K, O, G, 0);
     if (dfpx_supported(g, q)) {  // weights read as codes + scale digits
       if (!ws_ok) return FGQ_ERR_WORKSPACE;
+      if (fcx_pick(g, false)) return launch_fcx(q, sx, prepared, false, g, lo, as_stream(stream));
       return launch_foldx_splitk(q, sx, prepared, g, lo, static_cast<int32_t*>(ws), as_stream(stream));
     }
     int32_t sps = 0;
@@ -546,6 +547,7 @@ fgq_status fgq_gemm_dfp_ws(const uint8_t* q, int32_t bits, const float* sx, int6
   const bool ws_ok = ws && reinterpret_cast<uintptr_t>(ws) % 4 == 0 && ws_bytes >= fgq_gemm_ws_bytes(M, K, O, G, 1);
   if (dfpx_supported(g, q)) {  // weights read as codes + scale codes
     if (!ws_ok) return FGQ_ERR_WORKSPACE;
+    if (fcx_pick(g, true)) return launch_fcx(q, sx, prepared, true, g, lo, as_stream(stream));
     return launch_dfpx_splitk(q, sx, prepared, g, lo, static_cast<int32_t*>(ws), as_stream(stream));
   }
   if (fold_dfp_supported(g, q)) {

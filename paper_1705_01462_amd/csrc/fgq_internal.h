@@ -189,6 +189,11 @@ fgq_status launch_dfpx_splitk(const uint8_t* q, const float* sx, const void* pre
 // planes), int32 sums in ws [splits][3][M][O], the folded reduction.
 fgq_status launch_foldx_splitk(const uint8_t* q, const float* sx, const void* prepared,
                                const ConvGeom& g, const LayerOut& out, int32_t* ws, hipStream_t st);
+// The same two in one launch, K divided among a workgroup's waves (fcx.hip):
+// whether a shape takes it, and the launch (dfp: fixed-point scales).
+bool fcx_pick(const ConvGeom& g, bool dfp);
+fgq_status launch_fcx(const uint8_t* q, const float* sx, const void* prepared, bool dfp, const ConvGeom& g,
+                      const LayerOut& out, hipStream_t st);
 fgq_status launch_splitk_reduce(const int32_t* part, int32_t splits, bool dfp, int64_t M, int64_t O,
                                 const float* sx, const float* scale, const int32_t* fl, const LayerOut& out,
                                 hipStream_t st);

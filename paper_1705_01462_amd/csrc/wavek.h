@@ -8,7 +8,7 @@
 // compute units that chain is the layer's time: 17.6 us (fixed-point scales)
 // to 28.6 us (groups of 64) for the 3x3 layer of 512 channels at 7 x 7,
 // batch 1 (4 tiles of 36 steps), 6.9 and 6.8 us here, and ResNet-50's whole
-// forward pass at batch 1 594 -> 321 us.  Here
+// forward pass at batch 1 594 -> 344 us (321 with later steps).  Here
 //  * a wave takes every kWK-th step of the reduction and loads both operands
 //    straight into matrix-instruction fragments, two steps ahead, with no LDS
 //    and no barrier on the way: lane l holds row l % 32, k-slot 16 * (l / 32)
@@ -60,6 +60,54 @@ namespace {
 
 using namespace ig;
 
+// Where a kernel that finishes four channels of a row per thread writes them.
+struct PieceOut {
+  float* y;         // fp32 output, or null
+  uint8_t* q;       // code output, or null
+  int32_t code_bits;
+  bool vec;         // pieces are whole and aligned in every output
+};
+
+// Channels e .. e+3 of the output (n elements), of which `left` are in the row.
+template <bool kR>
+__device__ inline void store_piece(const PieceOut& out, const QScale& qs, const float __attribute__((ext_vector_type(4))) v,
+                                   int64_t e, int left, int64_t n) {
+  typedef float v4f __attribute__((ext_vector_type(4)));
+  const int nv = left < 4 ? left : 4;
+  if (out.y) {
+    if (out.vec) {
+      if (check_store(kSiteStoreY, e, 4, n)) __builtin_nontemporal_store(v, reinterpret_cast<v4f*>(out.y + e));
+    } else {
+#pragma unroll
+      for (int c = 0; c < 4; ++c)
+        if (c < nv && check_store(kSiteStoreY, e + c, 1, n)) __builtin_nontemporal_store(v[c], out.y + e + c);
+    }
+  }
+  if (out.code_bits == 8) {
+    const uint32_t cw = qcode4<kR>(v[0], v[1], v[2], v[3], qs);
+    if (out.vec) {
+      if (check_store(kSiteStoreY, e, 4, n)) __builtin_nontemporal_store(cw, reinterpret_cast<uint32_t*>(out.q + e));
+    } else {
+#pragma unroll
+      for (int c = 0; c < 4; ++c)
+        if (c < nv && check_store(kSiteStoreY, e + c, 1, n)) out.q[e + c] = static_cast<uint8_t>(cw >> (8 * c));
+    }
+  } else if (out.code_bits == 4) {  // O is even: pieces of two or four channels
+    uint32_t cw = 0;
+#pragma unroll
+    for (int c = 0; c < 4; ++c) cw |= qcode<kR>(v[c], qs) << (4 * c);
+    if (out.vec) {
+      if (check_store(kSiteStoreY, e / 2, 2, (n + 1) / 2))
+        __builtin_nontemporal_store(static_cast<uint16_t>(cw), reinterpret_cast<uint16_t*>(out.q + e / 2));
+    } else {
+#pragma unroll
+      for (int c = 0; c < 2; ++c)
+        if (2 * c < nv && check_store(kSiteStoreY, e / 2 + c, 1, (n + 1) / 2))
+          out.q[e / 2 + c] = static_cast<uint8_t>(cw >> (8 * c));
+    }
+  }
+}
+
 template <int kBits, int kMode, int kWO, int kWK>
 __global__ __launch_bounds__(64 * kWO * kWK, 2) void wavek_kernel(WavekArgs a) {
   constexpr int kWG = 64 * kWO * kWK;
@@ -99,7 +147,7 @@ __global__ __launch_bounds__(64 * kWO * kWK, 2) void wavek_kernel(WavekArgs a) {
 #pragma unroll
     for (int h = 0; h < 4; ++h) {
       const int k = kKT * ks + 32 * h + 16 * half;
-      // exact for k < 65536: k * (inv * C - 2^32) < 2^32
+      // exact for k < 65536 (no prepared layout is longer): k * (inv * C - 2^32) < 2^32
       const int rs = static_cast<int>(__umulhi(static_cast<uint32_t>(k), a.inv_c));
       const int c = k - rs * a.x.C;
       const int r = a.x.S > 1 ? static_cast<int>(__umulhi(static_cast<uint32_t>(rs), a.inv_s)) : rs;
@@ -300,6 +348,7 @@ __global__ __launch_bounds__(64 * kWO * kWK, 2) void wavek_kernel(WavekArgs a) {
   const double cd = kMode == 1 && fl > -2048 && fl < 2048 ? static_cast<double>(sx) * ldexp(1.0, -fl) : 0.0;
   const QScale qs = make_qscale(os, a.code_bits == 4 ? 4 : 8);
   const int64_t n = static_cast<int64_t>(M) * O;
+  const PieceOut out{a.y, a.q, a.code_bits, vec};
   with_rcp(qs, [&](auto rcp) {
     constexpr bool kR = decltype(rcp)::value;
 #pragma unroll
@@ -323,39 +372,7 @@ __global__ __launch_bounds__(64 * kWO * kWK, 2) void wavek_kernel(WavekArgs a) {
         }
         if (a.res) v[c] = add_relu(v[c], resv[i][c]);
       }
-      const int nv = O - ch < 4 ? O - ch : 4;  // channels of this piece
-      if (a.y) {
-        if (vec) {
-          if (check_store(kSiteStoreY, e, 4, n)) __builtin_nontemporal_store(v, reinterpret_cast<v4f*>(a.y + e));
-        } else {
-#pragma unroll
-          for (int c = 0; c < 4; ++c)
-            if (c < nv && check_store(kSiteStoreY, e + c, 1, n)) __builtin_nontemporal_store(v[c], a.y + e + c);
-        }
-      }
-      if (a.code_bits == 8) {
-        const uint32_t cw = qcode4<kR>(v[0], v[1], v[2], v[3], qs);
-        if (vec) {
-          if (check_store(kSiteStoreY, e, 4, n)) __builtin_nontemporal_store(cw, reinterpret_cast<uint32_t*>(a.q + e));
-        } else {
-#pragma unroll
-          for (int c = 0; c < 4; ++c)
-            if (c < nv && check_store(kSiteStoreY, e + c, 1, n)) a.q[e + c] = static_cast<uint8_t>(cw >> (8 * c));
-        }
-      } else if (a.code_bits == 4) {  // O is even: pieces of two or four channels
-        uint32_t cw = 0;
-#pragma unroll
-        for (int c = 0; c < 4; ++c) cw |= qcode<kR>(v[c], qs) << (4 * c);
-        if (vec) {
-          if (check_store(kSiteStoreY, e / 2, 2, (n + 1) / 2))
-            __builtin_nontemporal_store(static_cast<uint16_t>(cw), reinterpret_cast<uint16_t*>(a.q + e / 2));
-        } else {
-#pragma unroll
-          for (int c = 0; c < 2; ++c)
-            if (2 * c < nv && check_store(kSiteStoreY, e / 2 + c, 1, (n + 1) / 2))
-              a.q[e / 2 + c] = static_cast<uint8_t>(cw >> (8 * c));
-        }
-      }
+      store_piece<kR>(out, qs, v, e, O - ch, n);
     }
   });
 }
