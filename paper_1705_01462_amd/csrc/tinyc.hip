@@ -170,8 +170,9 @@ __global__ __launch_bounds__(kThreads, 3) void tinyc_kernel(TinyArgs a) {
 
   const double cd = fl > -2048 && fl < 2048 ? static_cast<double>(sx) * ldexp(1.0, -fl) : 0.0;
   const float cf = static_cast<float>(cd);
-  // (the code's v * y stays finite too: |v| < 2^24 cf, y = 1 / os)
-  const bool fast = static_cast<double>(cf) == cd && (kOut == 0 || cf * 16777216.0f / os < __builtin_huge_valf());
+  // (the code's v * y stays finite too, whatever the sign of s_x: |v| < 2^24 |cf|, y = 1 / os)
+  const bool fast =
+      static_cast<double>(cf) == cd && (kOut == 0 || fabsf(cf) * 16777216.0f / os < __builtin_huge_valf());
   __syncthreads();  // the weights are read; the patches take their place
   publish(0);
   __syncthreads();

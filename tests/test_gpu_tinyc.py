@@ -93,3 +93,19 @@ def test_scale_outside_fp32():
     y = fgq.fgq_conv2d_w8(dev(q).view(-1), 8, dev(np.array([sx])), (B, H, W, 4), fgq.fgq_prepare_weights_w8(dev(w)), O,
                           R, S, st, pad)
     np.testing.assert_array_equal(y.cpu().numpy().reshape(ref.shape).view(np.uint32), ref.view(np.uint32))
+
+
+@pytest.mark.parametrize("sx,so", [(-1e30, 1e-10), (1e30, 1e-10), (-0.0117, 0.02), (0.0117, 1e-37), (-0.0117, 1e-37)])
+def test_codes_of_any_quotient(sx, so):
+    # quotients y / so past fp32 on either side, also by a negative s_x:
+    # saturated codes, as the quantization of the fp32 output gives
+    case = CASES[8]
+    B, H, W, O, R, S, st, pad = case
+    w = fi.rng("tinyc-sign", O, R).standard_normal((O, 4, R, S)).astype(np.float32)
+    q, prep = dev(image(case)).view(-1), fgq.fgq_prepare_weights_w8(dev(w))
+    args = (q, 8, dev(np.array([sx], np.float32)), (B, H, W, 4), prep, O, R, S, st, pad)
+    y = fgq.fgq_conv2d_w8(*args)
+    scale = dev(np.array([so], np.float32))
+    for bits in (8, 4):
+        want, _ = fgq.fgq_quantize_act(y, bits, scale_in=scale)
+        assert torch.equal(fgq.fgq_conv2d_w8(*args, bits, scale).view(-1), want), bits
