@@ -236,6 +236,11 @@ __global__ __launch_bounds__(kThreads, 3) void tinyc_kernel(TinyArgs a) {
       else
         fill(std::false_type{});
     });
+    // Lanes read pieces that other lanes of the wave wrote: LDS serves a wave
+    // in order, and the fence keeps the compiler from moving the reads up.
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
     if (ho < a.x.Ho) {
       const int64_t e0 = (static_cast<int64_t>(n.b * a.x.Ho + ho) * a.x.Wo + wo0) * a.x.O + og;
       const int64_t nbytes = static_cast<int64_t>(a.x.M) * a.x.O * kEsz / 8;

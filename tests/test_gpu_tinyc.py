@@ -1,9 +1,12 @@
 """The first layer on four-channel 8-bit images: 8-bit weights and fixed-point
-scales, bit for bit against the oracle.  Output widths on both sides of a
-unit's 32, 64 and 128 pixels, rows that end inside a unit, filters that fill
-their form's pieces and that do not, a scale outside fp32 (the fp64 scaling), output
-channels that are not whole tiles, fp32, 8- and 4-bit outputs, and outputs the
-form refuses (the tiled kernel).  Images hold 0 and 255 at their borders."""
+scales, bit for bit against the oracle.  ROWS are layers the row-staging kernel
+takes (its rule is repeated here, so a change of the rule shows): one, two and
+four output rows a unit, several units a workgroup in uneven runs, several
+units a row, rows that end inside a unit, filters that fill their form's pieces
+and that do not, output channels that are not whole tiles.  TILED are layers it
+leaves to the tiled kernel, for their filter, patch, fill or outputs.  fp32, 8-
+and 4-bit outputs, scales outside fp32 (the fp64 scaling) and quotients outside
+fp32.  Images hold 0 and 255 at their borders."""
 import numpy as np
 import pytest
 import torch
@@ -21,22 +24,51 @@ def dev(a):
     return torch.from_numpy(np.ascontiguousarray(a)).cuda()
 
 
-# B, H, W, O, R, S, stride (h, w), pad (h, w)
-CASES = [
-    (2, 31, 45, 64, 7, 7, (2, 2), (3, 3)),      # 23 wide: four rows a unit
-    (1, 20, 130, 64, 7, 7, (2, 2), (3, 3)),     # 65 wide
-    (1, 9, 259, 32, 7, 7, (2, 2), (3, 3)),      # 130 wide: a second unit of two pixels
-    (1, 12, 64, 96, 3, 3, (1, 1), (1, 1)),
-    (1, 13, 33, 16, 4, 4, (1, 3), (2, 0)),
-    (1, 11, 40, 80, 5, 5, (1, 1), (2, 2)),
-    (2, 51, 63, 96, 11, 11, (4, 4), (0, 0)),
+# B, H, W, O, R, S, stride (h, w), pad (h, w); units and workgroups of them on
+# 256 compute units
+ROWS = [
+    (1, 12, 64, 96, 3, 3, (1, 1), (1, 1)),      # two rows a unit
+    (1, 13, 33, 16, 4, 4, (1, 3), (2, 0)),      # four; whole 8-bit pieces, no 4-bit ones
+    (2, 30, 250, 64, 7, 7, (2, 2), (3, 3)),     # 125 wide: one row
+    (1, 9, 130, 64, 3, 3, (1, 1), (1, 1)),      # 130 wide: a second unit of two pixels
+    (2, 9, 29, 48, 5, 5, (1, 1), (2, 2)),       # four rows of eight taps, 29 wide
+    (1, 11, 57, 80, 5, 5, (1, 1), (2, 2)),      # two rows, 57 wide
+    (1, 10, 243, 32, 7, 8, (1, 1), (3, 4)),     # the form's whole weights; 244 wide, two units
+    (16, 81, 80, 32, 5, 5, (1, 1), (2, 2)),     # 80 wide, 1296 units on 768
+    (5, 61, 33, 1024, 3, 3, (1, 1), (1, 1)),    # 155 units on 48 workgroups: runs of three and four
+    (3, 61, 57, 1024, 5, 5, (1, 1), (2, 2)),    # 93 on 48
+    (1, 16, 20, 100, 3, 3, (1, 1), (1, 1)),     # whole fp32 pieces, no whole code pieces
+]
+TILED = [
+    (2, 31, 45, 64, 7, 7, (2, 2), (3, 3)),      # a patch of 13 rows
+    (1, 20, 130, 64, 7, 7, (2, 2), (3, 3)),     # 65 wide: units mostly empty
+    (1, 9, 259, 32, 7, 7, (2, 2), (3, 3)),      # 130 wide, the same
+    (1, 11, 40, 80, 5, 5, (1, 1), (2, 2)),      # 40 wide, the same
+    (2, 51, 63, 96, 11, 11, (4, 4), (0, 0)),    # no form
     (1, 30, 70, 32, 11, 12, (2, 1), (5, 6)),    # no form
-    (2, 30, 250, 64, 7, 7, (2, 2), (3, 3)),     # 125 wide: a full unit
-    (40, 21, 9, 48, 7, 8, (1, 2), (3, 4)),      # many images, units mostly empty
-    (1, 16, 20, 100, 7, 7, (2, 2), (3, 3)),     # whole fp32 pieces, no whole code pieces
-    (1, 16, 20, 34, 3, 3, (1, 1), (1, 1)),      # neither
+    (40, 21, 9, 48, 7, 8, (1, 2), (3, 4)),      # a patch of ten rows
+    (1, 16, 20, 100, 7, 7, (2, 2), (3, 3)),     # a patch of 13 rows
+    (1, 16, 20, 34, 3, 3, (1, 1), (1, 1)),      # no whole pieces of any kind
     (1, 40, 20, 32, 13, 13, (1, 1), (6, 6)),    # no form
 ]
+CASES = ROWS + TILED
+
+
+def takes(case, out_bits):
+    """Whether the row-staging kernel takes the layer, and its workgroups'
+    units as (units, workgroups)."""
+    B, H, W, O, R, S, (sh, sw), (ph, pw) = case
+    Ho, Wo = fgq.conv_out_hw(H, W, R, S, (sh, sw), (ph, pw))
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    form = 1 if S <= 4 and R <= 4 else 2 if S <= 8 and R <= 7 else 0
+    pxw = 1 if Wo <= 32 else 2 if Wo <= 64 else 4
+    rows = 4 // pxw
+    segs = -(-Wo // (32 * pxw))
+    units = B * -(-Ho // rows) * segs
+    fits = (rows - 1) * sh + R <= 8 and (pxw * 32 - 1) * sw + 4 * form <= 320
+    whole = O % (4 if out_bits == 0 else 128 // out_bits) == 0
+    full = form == 1 or 8 * Wo >= 7 * 32 * pxw * segs or units > 5 * cus
+    return form > 0 and fits and whole and full, (units, min(units, 3 * cus // -(-O // 64)))
 
 
 def image(case):
@@ -55,6 +87,16 @@ def check(layer, ref, O, tag):
         assert torch.equal(layer(bits, so).view(-1), want), tag
 
 
+def test_which_kernel():
+    for case in ROWS:
+        assert takes(case, 0)[0], case
+    for case in TILED:
+        assert not any(takes(case, b)[0] for b in (0, 8, 4)), case
+    assert all(any(takes(c, b)[0] for c in ROWS) for b in (8, 4))
+    runs = [takes(c, 0)[1] for c in ROWS]
+    assert any(u > 3 * g and u % g for u, g in runs)  # third and fourth units of uneven runs
+
+
 @pytest.mark.parametrize("case", CASES)
 def test_w8(case):
     B, H, W, O, R, S, st, pad = case
@@ -68,7 +110,7 @@ def test_w8(case):
                                           b, so), ref, O, "w8")
 
 
-@pytest.mark.parametrize("case", CASES[:2] + CASES[8:9])
+@pytest.mark.parametrize("case", ROWS[:4] + ROWS[5:6] + TILED[:2])
 def test_fixed_point(case):
     B, H, W, O, R, S, st, pad = case
     w = fi.he_weights(O, 4, R, S, "tinyc")
@@ -82,24 +124,26 @@ def test_fixed_point(case):
                                            R, S, st, pad, 4, b, so), ref, O, "dfp")
 
 
-def test_scale_outside_fp32():
+@pytest.mark.parametrize("case", [ROWS[0], ROWS[2], TILED[0]])
+def test_scale_outside_fp32(case):
     # s_x 2^-fl below the fp32 range: the fp64 scaling decides the result
-    case = CASES[0]
     B, H, W, O, R, S, st, pad = case
     w = fi.rng("tinyc-tiny", O, R).standard_normal((O, 4, R, S)).astype(np.float32) * np.float32(1e-30)
     W8, fl = oracle.w8_quantize(w)
     q, sx = image(case), np.float32(3e-17)
+    cd = np.float64(sx) * 2.0 ** -fl
+    assert np.float64(np.float32(cd)) != cd
     ref = oracle.conv2d_w8(q.reshape(-1), 8, sx, (B, H, W, 4), W8, fl, O, R, S, st, pad)
-    y = fgq.fgq_conv2d_w8(dev(q).view(-1), 8, dev(np.array([sx])), (B, H, W, 4), fgq.fgq_prepare_weights_w8(dev(w)), O,
-                          R, S, st, pad)
-    np.testing.assert_array_equal(y.cpu().numpy().reshape(ref.shape).view(np.uint32), ref.view(np.uint32))
+    prep = fgq.fgq_prepare_weights_w8(dev(w))
+    check(lambda b, so: fgq.fgq_conv2d_w8(dev(q).view(-1), 8, dev(np.array([sx])), (B, H, W, 4), prep, O, R, S, st, pad,
+                                          b, so), ref, O, "tiny")
 
 
 @pytest.mark.parametrize("sx,so", [(-1e30, 1e-10), (1e30, 1e-10), (-0.0117, 0.02), (0.0117, 1e-37), (-0.0117, 1e-37)])
 def test_codes_of_any_quotient(sx, so):
     # quotients y / so past fp32 on either side, also by a negative s_x:
     # saturated codes, as the quantization of the fp32 output gives
-    case = CASES[8]
+    case = ROWS[2]
     B, H, W, O, R, S, st, pad = case
     w = fi.rng("tinyc-sign", O, R).standard_normal((O, 4, R, S)).astype(np.float32)
     q, prep = dev(image(case)).view(-1), fgq.fgq_prepare_weights_w8(dev(w))
