@@ -130,8 +130,9 @@ struct ResTile {
         const int m = m0 + (lr / 32) * kNB * 32 + 32 * (c0 + c) + lr % 32;
         const int ch = ot0 + cb * T::kChanPerChunk;
         v[c][i] = u32x4{0, 0, 0, 0};
-        if (m < M && ch < O)
-          v[c][i] = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(res + static_cast<int64_t>(m) * O + ch));
+        const int64_t e = static_cast<int64_t>(m) * O + ch;
+        if (m < M && ch < O && check_store(kSiteStoreY, e, 4, static_cast<int64_t>(M) * O))  // the output's extent
+          v[c][i] = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(res + e));
       }
     }
   }

@@ -232,11 +232,12 @@ __global__ __launch_bounds__(64 * kWO * kWK, 2) void wavek_kernel(WavekArgs a) {
     for (int j = 0; j < kPlanes; ++j) biasv[i][j] = v4i{0, 0, 0, 0};
     if (a.res && in) {
       if (vec) {
-        if (ch < O) resv[i] = __builtin_nontemporal_load(reinterpret_cast<const v4f*>(a.res + e));
+        if (ch < O && check_store(kSiteStoreY, e, 4, static_cast<int64_t>(M) * O))  // the output's extent
+          resv[i] = __builtin_nontemporal_load(reinterpret_cast<const v4f*>(a.res + e));
       } else {
 #pragma unroll
         for (int c = 0; c < 4; ++c)
-          if (ch + c < O) resv[i][c] = a.res[e + c];
+          if (ch + c < O && check_store(kSiteStoreY, e + c, 1, static_cast<int64_t>(M) * O)) resv[i][c] = a.res[e + c];
       }
     }
     if constexpr (kMode != 2) {
