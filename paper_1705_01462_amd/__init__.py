@@ -121,8 +121,14 @@ def fgq_check_violations():
 # them), a tensor that is as it should be takes one line, and the stream is the
 # raw handle instead of a Stream object.  A 64x256x128 product, whose kernel
 # takes 4.8 us: 10.1 -> 6.1 us a call.
-def _stream():
-    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+try:
+    from torch._C import _cuda_getCurrentRawStream, _cuda_getDevice
+
+    def _stream():
+        return _cuda_getCurrentRawStream(_cuda_getDevice())
+except ImportError:  # a torch without these two (they are not part of its public interface)
+    def _stream():
+        return torch.cuda.current_stream().cuda_stream
 
 
 def _dev(t, dtype, name):

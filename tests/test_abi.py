@@ -247,3 +247,23 @@ def test_residual_validation():
     assert dr(8, P, None, P) == 1                                       # q_out for codes
     assert dr(6, P, P, P) == 4                                          # out_bits
     assert dr(0, None, None, ctypes.c_void_p(0x1001)) == 8              # prepared alignment
+
+
+@pytest.mark.parametrize("present", [True, False])
+def test_stream_handle_with_and_without_the_raw_getters(present, monkeypatch):
+    """The current stream's handle comes from two private functions of torch
+    where they exist, and from torch.cuda.current_stream() otherwise."""
+    import importlib.util
+    import types
+
+    import torch
+    for name, fn in (("_cuda_getDevice", lambda: 3), ("_cuda_getCurrentRawStream", lambda dev: 100 + dev)):
+        if present:
+            monkeypatch.setattr(torch._C, name, fn, raising=False)
+        else:
+            monkeypatch.delattr(torch._C, name, raising=False)
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda: types.SimpleNamespace(cuda_stream=7))
+    spec = importlib.util.spec_from_file_location("fgq_binding_copy", fgq.__file__)
+    mod = importlib.util.module_from_spec(spec)
+    spec.loader.exec_module(mod)
+    assert mod._stream() == (103 if present else 7)
