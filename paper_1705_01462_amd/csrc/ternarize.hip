@@ -498,7 +498,14 @@ fgq_status launch_ternarize(const float* w, int64_t O, int64_t C, int32_t R,
   const int64_t K = static_cast<int64_t>(R) * S * C;
   // One lane per group where a group's weights fit registers and one run of
   // G channels with all its taps fits the LDS tile; the asymmetric search
-  // and other group sizes take the general kernel.
+  // and other group sizes take the general kernel.  So do rows of very few
+  // groups (small C, one tap): a workgroup takes one row here, so most of its
+  // lanes idle, where the general kernel packs rows into a wave (65536 rows,
+  // exact rule, us general -> here: G = 16, 1 group a row 92 -> 189, 2 148 ->
+  // 191, 4 285 -> 192; G = 8, 1 group 70 -> 96, 2 106 -> 96; G = 4, 1 group
+  // 62 -> 64, 1M rows 551 -> 540; by the Gauss rule only G = 16, 1 group, 86
+  // -> 89), and layers of so many rows that their workgroups' threads pass the
+  // 2^32 of a launch dimension.
   const int64_t RS = static_cast<int64_t>(R) * S;
   if (method != kTernAsym && (G == 4 || G == 8 || G == 16) && G * RS <= kTileFloats && C < (1LL << 31)) {
     // half-full tiles at 3x3 leave eight workgroups a unit to overlap
@@ -506,7 +513,8 @@ fgq_status launch_ternarize(const float* w, int64_t O, int64_t C, int32_t R,
     if (tc < G) tc = G;
     if (tc > C) tc = C;
     const int64_t nct = ceil_div(C, tc);
-    if (O * nct <= 0x7fffffffLL) {
+    const int64_t few = method == FGQ_TERN_EXACT ? G / 8 : (method == FGQ_TERN_GAUSS ? G / 16 : 0);
+    if (tc / G * RS > few && O * nct < (1LL << 32) / kTileThreads) {
       const uint32_t grid = static_cast<uint32_t>(O * nct);
       const int32_t c = static_cast<int32_t>(C), rs = static_cast<int32_t>(RS), t = static_cast<int32_t>(tc),
                     n = static_cast<int32_t>(nct);

@@ -1,7 +1,9 @@
 """fgq_ternarize where its one-lane-per-group tiles can go wrong: runs of
 channels that end inside a tile, tiles of one group, tap counts up to the tile
-limit and past it (the general kernel), and non-finite weights in the first,
-the last and an inner group.  Codes, scales and thresholds bit for bit."""
+limit and past it (the general kernel), rows of few groups on either side of
+the rule, more rows than a launch dimension holds workgroups of a tile, and
+non-finite weights in the first, the last and an inner group.  Codes, scales
+and thresholds bit for bit."""
 import numpy as np
 import pytest
 import torch
@@ -25,6 +27,12 @@ METHODS = [oracle.EXACT, oracle.EXP_LEMMA, oracle.GAUSS]
     ((2, 32, 12, 12), 16),   # 16 * 144 = 2304 floats: one group's taps fill the tile
     ((2, 16, 13, 13), 16),   # 16 * 169 floats: past it, the general kernel
     ((1, 4, 1, 1), 4),
+    ((70, 16, 1, 1), 16),    # one, two and three groups a row
+    ((70, 32, 1, 1), 16),
+    ((70, 48, 1, 1), 16),
+    ((70, 16, 1, 2), 16),    # one group, two taps
+    ((70, 8, 1, 1), 8),
+    ((70, 16, 1, 1), 8),
 ])
 def test_tiles_bit_exact(shape, G, method):
     w = fi.rng("tern-tile", *shape, G).standard_normal(shape).astype(np.float32) * np.float32(0.05)
@@ -36,6 +44,19 @@ def test_tiles_bit_exact(shape, G, method):
     np.testing.assert_array_equal(codes.cpu().numpy(), oracle.pack_codes(t))
     np.testing.assert_array_equal(alpha.cpu().numpy().view(np.uint32), a.view(np.uint32))
     np.testing.assert_array_equal(delta.cpu().numpy().view(np.uint32), d.view(np.uint32))
+
+
+def test_rows_past_a_launch_of_tiles():
+    # 2^24 rows of one group: a workgroup of 256 lanes each would be 2^32 threads
+    O = 1 << 24
+    w = torch.randn((O, 4, 1, 1), device="cuda", generator=torch.Generator(device="cuda").manual_seed(4))
+    codes, alpha, delta = fgq.fgq_ternarize(w, 4)
+    rows = np.unique(np.r_[0:500, O - 500:O, fi.rng("tern-rows").integers(0, O, 2000)])
+    at = torch.from_numpy(rows).cuda()
+    t, a, d = oracle.ternarize(w[at].cpu().numpy(), 4)
+    np.testing.assert_array_equal(codes.view(O, -1)[at].cpu().numpy(), oracle.pack_codes(t).reshape(len(rows), -1))
+    np.testing.assert_array_equal(alpha.view(O, -1)[at].cpu().numpy().view(np.uint32), a.reshape(len(rows), -1).view(np.uint32))
+    np.testing.assert_array_equal(delta.view(O, -1)[at].cpu().numpy().view(np.uint32), d.reshape(len(rows), -1).view(np.uint32))
 
 
 @pytest.mark.parametrize("G", [4, 64])
