@@ -298,12 +298,63 @@ void tinyc_patch(const ConvGeom& g, int form, TinyArgs* a) {
   a->words = a->width * a->prows;
 }
 
+// Whether the form pays on a layer it fits.  Measured on some 3500 layers (3x3
+// to 7x7 filters, strides 1 to 4, 16 to 512 channels, 8 to 300 pixels a row, 1
+// to 64 images, every output kind; time here over the tiled kernel's):
+//  * Up to 64 channels.  Filters of form 1 gain (0.5 to 0.9) except where a
+//    second round of units is half empty (33 pixels in 64, 1088 units, 4x4:
+//    1.03 to 1.08) and on large fp32 outputs, bound by their stores (64
+//    channels, 5120 units 1.02 to 1.04, 7168 1.06 to 1.10).  7x7 filters gain
+//    where rows fill their units (112 pixels: 1 image 0.96, 8 0.94, 64 0.59) or
+//    there are several units a workgroup (80 pixels: 1280 units 1.00, 5120
+//    0.79); 64 fp32 channels on few units do not (28 units 1.02, 448 0.99).
+//    A reduction of one K step (5x5) is short for the tiled kernel too: up to
+//    32 channels 0.84 to 0.88 on few full units, but 1.0 to 1.17 on 448 to 896;
+//    from 1536 units on 0.7 to 0.9, with half-empty units (65 pixels) 1.05 to
+//    1.09; 64 channels of fp32 0.97 to 1.16.
+//  * More channels: the tiled kernel's tile has 128 of them, so it stages the
+//    image once for two workgroups here.  Codes of form 1: 0.5 to 0.97 where
+//    rows fill three quarters of their units (half: 1.04 to 1.22; five eighths
+//    0.7 to 0.97 from 5120 units on, 1280 up to 1.09), at stride 4 only past a
+//    round of units (28 units 1.03).  fp32 outputs: 0.85 to 0.99 up to two
+//    rounds, then up to 1.36.  7x7 codes: 112 units of 96 channels 1.14, 448
+//    1.20, 896 0.99, 448 of 192 0.88, 1792 of 128 0.86; fp32 up to 1.24.  5x5
+//    codes: 448 units of 256 channels 1.07, 896 0.93, 1792 of 128 0.92.  8-bit
+//    codes of 96 channels (rows that are not whole 64-byte pieces) 1.00 to 1.11
+//    at 7168 units.
+bool tinyc_pays(const ConvGeom& g, int form, int out_bits, const TinyArgs& a) {
+  const int64_t cus = device_cus();
+  const int64_t full = 32LL * a.pxw * ceil_div(g.Wo, 32 * a.pxw);  // pixels of a row's units
+  const int64_t units = g.B * ceil_div(g.Ho, a.rows) * (full / (32 * a.pxw));
+  const int64_t tiles = units * ceil_div(g.O, 64);
+  const auto filled = [&](int eighths) { return 8 * g.Wo >= eighths * full; };
+  const bool f32 = out_bits == 0, two_steps = g.K > 128;
+  if (g.O <= 64) {
+    if (form == 1) {
+      if (f32 && g.O > 32 && units > 16 * cus) return false;
+      return (g.O <= 32 && g.sh <= 3) || 16 * g.Wo >= 9 * full || units <= 3 * cus || units > 6 * cus;
+    }
+    if (two_steps) return (filled(7) && (!f32 || g.O <= 32 || units > cus)) || units > 5 * cus;
+    if (g.O <= 32 && units <= cus / 2) return filled(7);
+    return (g.O <= 32 || !f32) && units > 5 * cus && filled(5);
+  }
+  if (out_bits == 8 && g.O % 64 != 0 && units > 16 * cus) return false;
+  if (form == 1) {
+    if (g.sh > 3 && tiles <= cus) return false;
+    if (f32) return filled(6) && tiles <= 6 * cus;
+    return filled(6) || (filled(5) && units > 5 * cus);
+  }
+  if (f32) return false;
+  if (two_steps) return filled(units > 5 * cus ? 5 : 7) && tiles > 5 * cus;
+  return filled(7) && tiles > 12 * cus;
+}
+
 }  // namespace
 
-// Taken where its form fits: four 8-bit channels, outputs in whole aligned
-// 16-byte pieces, a patch within the registers that carry it.  Other first
-// layers (eight channels, 4-bit, three planes, residuals) stay with the tiled
-// kernel.
+// Taken where its form fits (four 8-bit channels, outputs in whole aligned
+// 16-byte pieces, a patch within the registers that carry it) and pays.  Other
+// first layers (eight channels, 4-bit, three planes, residuals) stay with the
+// tiled kernel.
 bool tinyc_supported(const ConvGeom& g, const uint8_t* q, const LayerOut& out) {
   if (g.C != 4 || g.bits != 8 || (out.bits != 0 && out.bits != 8 && out.bits != 4)) return false;
   const int form = tinyc_form(g);
@@ -316,11 +367,7 @@ bool tinyc_supported(const ConvGeom& g, const uint8_t* q, const LayerOut& out) {
   if (g.O % per != 0 || reinterpret_cast<uintptr_t>(p) % 16 != 0) return false;
   const int64_t segs = ceil_div(g.Wo, 32 * a.pxw), units = g.B * ceil_div(g.Ho, a.rows) * segs;
   if (units >= (1LL << 31) || ceil_div(g.O, 64) > device_cus()) return false;
-  // 7x7 (us, tiled -> here, codes out): rows that fill their units gain at
-  // every batch (112 pixels: 1 image 7.4 -> 7.0, 8 13.4 -> 12.5, 64 60 -> 35);
-  // 80 pixels in units of 128 only once there are several units per
-  // workgroup (640 units 9.6 -> 10.8, 1280 13.7 -> 13.5, 2560 21.9 -> 18.7).
-  return form == 1 || 8 * g.Wo >= 7 * 32 * a.pxw * segs || units > 5 * device_cus();
+  return tinyc_pays(g, form, out.bits, a);
 }
 
 fgq_status launch_tinyc(const uint8_t* q, const float* sx, const void* prepared, const ConvGeom& g,

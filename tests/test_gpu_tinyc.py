@@ -29,15 +29,15 @@ def dev(a):
 ROWS = [
     (1, 12, 64, 96, 3, 3, (1, 1), (1, 1)),      # two rows a unit
     (1, 13, 33, 16, 4, 4, (1, 3), (2, 0)),      # four; whole 8-bit pieces, no 4-bit ones
-    (2, 30, 250, 64, 7, 7, (2, 2), (3, 3)),     # 125 wide: one row
+    (20, 30, 250, 64, 7, 7, (2, 2), (3, 3)),    # 125 wide: one row, 300 units
     (1, 9, 130, 64, 3, 3, (1, 1), (1, 1)),      # 130 wide: a second unit of two pixels
-    (2, 9, 29, 48, 5, 5, (1, 1), (2, 2)),       # four rows of eight taps, 29 wide
-    (1, 11, 57, 80, 5, 5, (1, 1), (2, 2)),      # two rows, 57 wide
+    (2, 9, 29, 32, 5, 5, (1, 1), (2, 2)),       # four rows of eight taps, 29 wide
+    (1, 11, 57, 16, 5, 5, (1, 1), (2, 2)),      # two rows, 57 wide
     (1, 10, 243, 32, 7, 8, (1, 1), (3, 4)),     # the form's whole weights; 244 wide, two units
-    (16, 81, 80, 32, 5, 5, (1, 1), (2, 2)),     # 80 wide, 1296 units on 768
-    (5, 61, 33, 1024, 3, 3, (1, 1), (1, 1)),    # 155 units on 48 workgroups: runs of three and four
-    (3, 61, 57, 1024, 5, 5, (1, 1), (2, 2)),    # 93 on 48
-    (1, 16, 20, 100, 3, 3, (1, 1), (1, 1)),     # whole fp32 pieces, no whole code pieces
+    (24, 81, 80, 32, 5, 5, (1, 1), (2, 2)),     # 80 wide, 1944 units on 768: runs of two and three
+    (3, 41, 57, 1024, 3, 3, (1, 1), (1, 1)),    # 63 units on 48 workgroups
+    (5, 61, 57, 1024, 3, 3, (1, 1), (1, 1)),    # 155: runs of three and four; fp32 tiled
+    (1, 16, 28, 100, 3, 3, (1, 1), (1, 1)),     # whole fp32 pieces, no whole code pieces
 ]
 TILED = [
     (2, 31, 45, 64, 7, 7, (2, 2), (3, 3)),      # a patch of 13 rows
@@ -50,6 +50,9 @@ TILED = [
     (1, 16, 20, 100, 7, 7, (2, 2), (3, 3)),     # a patch of 13 rows
     (1, 16, 20, 34, 3, 3, (1, 1), (1, 1)),      # no whole pieces of any kind
     (1, 40, 20, 32, 13, 13, (1, 1), (6, 6)),    # no form
+    (2, 9, 29, 48, 5, 5, (1, 1), (2, 2)),       # one K step, few units
+    (5, 21, 33, 256, 3, 3, (1, 1), (1, 1)),     # 33 wide, more than 64 channels
+    (1, 30, 250, 128, 7, 7, (2, 2), (3, 3)),    # few units of 128 channels
 ]
 CASES = ROWS + TILED
 
@@ -65,10 +68,30 @@ def takes(case, out_bits):
     rows = 4 // pxw
     segs = -(-Wo // (32 * pxw))
     units = B * -(-Ho // rows) * segs
+    tiles = units * -(-O // 64)
     fits = (rows - 1) * sh + R <= 8 and (pxw * 32 - 1) * sw + 4 * form <= 320
     whole = O % (4 if out_bits == 0 else 128 // out_bits) == 0
-    full = form == 1 or 8 * Wo >= 7 * 32 * pxw * segs or units > 5 * cus
-    return form > 0 and fits and whole and full, (units, min(units, 3 * cus // -(-O // 64)))
+    full, f32, two_steps = 32 * pxw * segs, out_bits == 0, 4 * R * S > 128
+    if O <= 64 and form == 1:
+        pays = (O <= 32 and sh <= 3) or 16 * Wo >= 9 * full or units <= 3 * cus or units > 6 * cus
+        pays &= not f32 or O <= 32 or units <= 16 * cus
+    elif O <= 64 and two_steps:
+        pays = (8 * Wo >= 7 * full and (not f32 or O <= 32 or units > cus)) or units > 5 * cus
+    elif O <= 32 and units <= cus // 2:
+        pays = 8 * Wo >= 7 * full
+    elif O <= 64:
+        pays = (O <= 32 or not f32) and units > 5 * cus and 8 * Wo >= 5 * full
+    elif out_bits == 8 and O % 64 and units > 16 * cus:
+        pays = False
+    elif form == 1 and f32:
+        pays = 8 * Wo >= 6 * full and tiles <= 6 * cus and (sh <= 3 or tiles > cus)
+    elif form == 1:
+        pays = (8 * Wo >= 6 * full or (8 * Wo >= 5 * full and units > 5 * cus)) and (sh <= 3 or tiles > cus)
+    elif two_steps:
+        pays = not f32 and 8 * Wo >= (5 if units > 5 * cus else 7) * full and tiles > 5 * cus
+    else:
+        pays = not f32 and 8 * Wo >= 7 * full and tiles > 12 * cus
+    return form > 0 and fits and whole and pays, (units, min(units, 3 * cus // -(-O // 64)))
 
 
 def image(case):
@@ -89,12 +112,14 @@ def check(layer, ref, O, tag):
 
 def test_which_kernel():
     for case in ROWS:
-        assert takes(case, 0)[0], case
+        assert any(takes(case, b)[0] for b in (0, 8, 4)), case
     for case in TILED:
         assert not any(takes(case, b)[0] for b in (0, 8, 4)), case
-    assert all(any(takes(c, b)[0] for c in ROWS) for b in (8, 4))
-    runs = [takes(c, 0)[1] for c in ROWS]
-    assert any(u > 3 * g and u % g for u, g in runs)  # third and fourth units of uneven runs
+    for b in (0, 8, 4):  # workgroups of two and three units, either form
+        for R in (3, 5):
+            runs = [takes(c, b)[1] for c in ROWS if c[4] == R and takes(c, b)[0]]
+            assert any(u > g and u % g for u, g in runs), (b, R)
+    assert any(u > 3 * g for u, g in (takes(c, 8)[1] for c in ROWS))
 
 
 @pytest.mark.parametrize("case", CASES)
