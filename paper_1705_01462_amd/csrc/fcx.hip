@@ -11,7 +11,8 @@
 // channel (or row) l % 16; its quarter g = l / 16 of a fragment's 64 k is half
 // g % 2 of the pair's step g / 2, in the order the prepared layout stores
 // (xlayout.h); the order of k inside a sum is free as long as both operands
-// agree.  Weights are read once over the launch; the rows are read once per
+// agree.  Weights are read once per 32 rows (more rows: by two workgroups,
+// neighbours, so the second time from L2); the rows are read once per
 // workgroup, from L2.
 //
 // The sums are integers, so the results are the split form's bit for bit.
@@ -210,28 +211,44 @@ fgq_status launch_rows(const FcxArgs& a, int G, hipStream_t st) {
 
 }  // namespace
 
-// Measured in a graph (us a call, split form with its reduction -> here; G = 4):
-//   three planes  M 1:  K 4096, O 4096 10.1 -> 4.6;  K 9216 18.9 -> 7.9;
-//                       K 16384, O 512 11.8 -> 8.8;  K 32768, O 128 13.8 -> 14.6
-//                 M 32: K 4096, O 4096 13.0 -> 7.5;  K 9216, O 256 11.5 -> 12.1;
-//                       K 4096, O 8000 15.9 -> 13.8; K 16384, O 512 13.6 -> 19.3
-//                 M 64: K 4096, O 4096 19.2 -> 13.2; O 8000 21.0 -> 25.6
-//   one plane     M 1:  K 4096, O 4096 6.6 -> 3.6;   K 9216, O 1000 7.0 -> 4.5;
-//                       K 16384, O 512 7.3 -> 6.0;   K 32768, O 128 8.1 -> 9.8
-//                 M 32: K 4096, O 4096 7.9 -> 6.7;   O 128 6.8 -> 6.8;
-//                       K 9216, O 1000 7.9 -> 11.3;  K 4096, O 8000 9.0 -> 10.7
-//                 M 64: K 2048, O 1000 7.8 -> 4.8;   K 4096, O 4096 9.8 -> 10.5
+// Measured in a graph (us a call, split form with its reduction -> here; G = 4,
+// 1150 shapes: 1 to 64 rows, K 256 to 16384, 64 to 24000 channels):
+//   three planes  M 1:  K 4096, O 4096 10.1 -> 4.6;  K 9216 18.9 -> 7.9
+//                 M 16: K 12288, O 128 11.8 -> 9.7;  K 16384, O 64 12.3 -> 11.9
+//                 M 32: K 4096, O 4096 13.0 -> 7.5, O 4112 13.1 -> 13.1, O 8000 16.8 -> 14.0
+//                       K 6144, O 5000 16.0 -> 17.3, O 6000 22.5 -> 17.8
+//                       K 8192, O 128 11.4 -> 11.3, O 4112 22.2 -> 21.4, O 8000 28.4 -> 23.3
+//                       K 9216, O 256 11.5 -> 12.1; K 16384, O 512 13.6 -> 19.3
+//                 M 64: K 4096, O 2080 15.1 -> 13.2, O 4096 18.7 -> 13.5, O 8000 21.0 -> 25.6
+//                       K 8192, O 1000 15.8 -> 12.0, O 4096 20.9 -> 22.1
+//                 M 48: K 6144, O 2080 15.8 -> 16.5, O 4096 18.6 -> 16.8
+//                 M 33: K 5120, O 2080 14.0 -> 15.2; K 8192, O 2080 15.7 -> 20.8
+//   one plane     M 1:  K 4096, O 4096 6.6 -> 3.6;   K 9216, O 1000 7.0 -> 4.5
+//                 M 16: K 8192, O 128 6.9 -> 6.4;    K 11264, O 64 7.6 -> 7.9
+//                       K 12288, O 64 7.3 -> 8.3, O 1024 7.7 -> 8.5, O 2048 8.2 -> 8.5, O 4096 10.6 -> 8.6
+//                 M 11: K 12288, O 64 to 4096 at or below the split form; M 12: O 64 7.1 -> 7.3
+//                 M 32: K 4096, O 128 6.8 -> 6.3, O 4096 8.0 -> 6.6, O 8000 9.0 -> 10.7
+//                       K 9216, O 1000 7.9 -> 11.3
+//                 M 64: K 4096, O 2048 8.5 -> 6.7, O 4096 9.8 -> 10.5
 // and eagerly one launch costs the host 3 us less than two.  A wave's rounds
 // of loads are a serial chain, longer the more rows a round has, so K is
 // bounded by the rows; every workgroup reads all its rows, so past 16 rows
-// the workgroups are bounded too.  (Four row blocks a workgroup instead of
-// two workgroups: 11.5 -> 19.5 us at M 64, K 9216, O 1000, one plane; whole 64-byte runs a load,
-// transposed between lanes: 2 to 10% slower.)
+// the workgroups are bounded too.  With three planes a second workgroup on a
+// unit is worth it up to 32 K steps; beyond, where the split form's own
+// workgroups need a second round, or (past 32 rows, to 48 steps) where it
+// writes the sums of many rows and channels.  (Four row blocks a workgroup instead of two
+// workgroups: 11.5 -> 19.5 us at M 64, K 9216, O 1000, one plane; whole
+// 64-byte runs a load, transposed between lanes: 2 to 10% slower.)
 bool fcx_pick(const ConvGeom& g, bool dfp) {
-  const int64_t nk = ceil_div(g.K, 128);
-  if (g.M <= 16) return nk <= (dfp ? 96 : 128);
+  const int64_t nk = ceil_div(g.K, 128), cus = device_cus();
+  if (g.M <= 16) return nk <= (dfp ? (g.M <= 11 || g.O > 2048 ? 96 : 80) : 128);
   const int64_t wgs = ceil_div(g.O, 16) * ceil_div(g.M, 32);
-  return dfp ? nk <= 32 && wgs <= device_cus() : nk <= 64 && wgs <= 2 * device_cus();
+  if (dfp) return nk <= 32 && wgs <= cus;
+  if (nk > 64 || wgs > 2 * cus) return false;
+  if (wgs <= cus || nk <= 32) return true;
+  int32_t sps = 0;
+  const int64_t split_wgs = ceil_div(g.O, 128) * dfpx_splits(g.M, g.K, g.O, g.G, &sps);
+  return split_wgs > cus || (g.M > 32 && nk <= 48 && g.M * g.O >= 1 << 17);
 }
 
 fgq_status launch_fcx(const uint8_t* q, const float* sx, const void* prepared, bool dfp, const ConvGeom& g,

@@ -33,6 +33,13 @@ CASES = [
     (20, 8192, 34, 4),     # 64 steps, more than 16 rows
     (20, 8320, 34, 4),
     (40, 256, 2080, 4),    # more workgroups than compute units
+    (12, 10240, 40, 4),    # 80 and 81 steps at 12 rows, and 81 with many channels:
+    (12, 10368, 40, 4),    #   the fixed-point rule's second line
+    (13, 10368, 2052, 4),
+    (33, 4224, 2080, 4),   # more than 32 rows, two rounds of workgroups, 33 steps:
+    (40, 4224, 3280, 4),   #   few and many sums
+    (20, 4224, 4112, 4),   # 20 rows, two rounds of workgroups, 33 steps and 64,
+    (17, 8192, 4112, 4),   #   where the split form needs two rounds itself
 ]
 
 
