@@ -537,8 +537,15 @@ fgq_status launch_cfg(const FoldArgs& a0, hipStream_t st) {
   // the other workgroup of the unit is that second set.  Three planes gain
   // nothing (196 tiles of 36 steps 30.2 -> 30.6, of 8 10.2 -> 12.0): their
   // steps are bound by matrix work and code expansion, not by the loads.
+  // fp32 outputs leave in one burst behind the exchange, so a short chain must
+  // save more: not at 5 steps (3 against 2.5 a set; 86 tiles 6.7 -> 6.8, 246
+  // tiles 6.6 -> 7.2), nor, with more than half the units busy, at 4, 6, 7 and
+  // 9 (246 tiles 6.2 -> 6.5, 6.9 -> 7.2, 7.0 -> 7.2, 8.2 -> 8.4; at 8 7.4 -> 7.3;
+  // 123 tiles of 4 to 9 other than 5: 0.94 to 1.00).
   if constexpr (kDfp && kOut != 1 && kNWO >= 2) {
-    if (a.x.C % 16 == 0 && n <= device_cus() && a.x.K > 3 * kKT) {
+    const int nk = (a.x.K + kKT - 1) / kKT;
+    const bool pays = kOut != 0 || nk > 9 || (2 * n <= device_cus() ? nk != 5 : nk == 8);
+    if (a.x.C % 16 == 0 && n <= device_cus() && a.x.K > 3 * kKT && pays) {
       if (a.x.C >= kKT)
         hipLaunchKernelGGL((fold_conv_kernel<kBits, kNWO, kNB, 0, kOut, kDfp, kG, 2>), grid, dim3(2 * kThreads), 0, st, a);
       else

@@ -129,8 +129,9 @@ def test_one_unaligned_output():
 @pytest.mark.parametrize("case", [
     (1, 47, 47, 128, 260, 3, 1),   # at most a tile per unit: two wave sets, 9 steps: 5 and 4
     (1, 53, 52, 448, 200, 1, 1),   # 3.5 steps: 2 and 2
-    (1, 77, 75, 48, 200, 3, 1),    # C < 128: 4 steps, the last not whole
+    (1, 77, 75, 48, 200, 3, 1),    # C < 128: 4 steps, the last not whole; fp32 in one set
     (1, 90, 96, 144, 64, 3, 1),    # two channel waves: 11 steps: 6 and 5
+    (1, 60, 60, 64, 200, 3, 1),    # 5 steps: two sets for codes and shortcuts, one for fp32
 ])
 def test_fixed_point_two_sets(case, bits):
     test_fixed_point(case, bits)
