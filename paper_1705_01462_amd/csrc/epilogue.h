@@ -75,42 +75,65 @@ struct OutPtrs {
 
 // Direct form: each lane stores its own values.  `val(c, r)` is the fp32
 // output of block c, accumulator r; lanes of channels >= O store nothing.
-template <int kOut, int kNB, bool kRcp, class Val>
+// Residual values are requested kBatch at a time: one at a time, each behind
+// the store before it, they were a chain of 32 memory latencies (fixed-point
+// scales, 24576 rows, 128 -> 589 channels: 56.5 -> 38.4 us; G = 64, 11664
+// rows, 576 -> 295: 27.7 -> 15.8; 360 rows, 128 -> 2046: 8.0 -> 5.7).
+template <int kOut, int kNB, bool kRcp, int kBatch = 16, class Val>
 __device__ inline void store_direct(const OutPtrs& out, const QScale& qs, int m_wave, int o, int lane, Val&& val) {
   constexpr int kCode = out_code_bits(kOut);
   if (o >= out.O) return;
+  const int64_t n = static_cast<int64_t>(out.M) * out.O;
+  // the lane's first element; its other rows are whole rows (the same for all lanes) further
+  const int ml = m_wave + 4 * (lane / 32);
+  const int64_t el = static_cast<int64_t>(ml) * out.O + o;
+  auto row = [](int i) { return 8 * (i / 4) + i % 4; };
 #pragma unroll
   for (int c = 0; c < kNB; ++c) {
 #pragma unroll
-    for (int r = 0; r < 16; ++r) {
-      const int m = m_wave + 32 * c + 8 * (r / 4) + 4 * (lane / 32) + (r % 4);
-      if (m >= out.M) continue;
-      const int64_t e = static_cast<int64_t>(m) * out.O + o;
-      const int64_t n = static_cast<int64_t>(out.M) * out.O;
-      float v = val(c, r);
+    for (int r0 = 0; r0 < 16; r0 += kBatch) {
+      float rv[out_res(kOut) ? kBatch : 1];
       if constexpr (out_res(kOut)) {
-        if (check_store(kSiteStoreY, e, 1, n)) v = add_relu(v, __builtin_nontemporal_load(out.res + e));
+#pragma unroll
+        for (int i = 0; i < kBatch; ++i) {
+          const int dm = 32 * c + row(r0 + i);
+          const int64_t e = el + static_cast<int64_t>(dm) * out.O;
+          rv[i] = 0.0f;
+          if (ml + dm < out.M && check_store(kSiteStoreY, e, 1, n)) rv[i] = __builtin_nontemporal_load(out.res + e);
+        }
+        // wait for them here, once: in the rows' branches below the compiler
+        // waits for everything outstanding, each row for the store before it
+#pragma unroll
+        for (int i = 0; i < kBatch; ++i) asm volatile("" : "+v"(rv[i]));
       }
-      if constexpr (out_f32(kOut)) {
-        if (check_store(kSiteStoreY, e, 1, n)) __builtin_nontemporal_store(v, out.y + e);
-      }
-      if constexpr (kCode == 8) {
-        if (check_store(kSiteStoreY, e, 1, n))
-          __builtin_nontemporal_store(static_cast<uint8_t>(qcode<kRcp>(v, qs)), out.q + e);
-      } else if constexpr (kCode == 4) {
-        const unsigned b = pair_nibbles(qcode<kRcp>(v, qs));
-        if ((o & 1) == 0 && check_store(kSiteStoreY, e >> 1, 1, (n + 1) / 2))
-          __builtin_nontemporal_store(static_cast<uint8_t>(b), out.q + (e >> 1));
+#pragma unroll
+      for (int i = 0; i < kBatch; ++i) {
+        const int dm = 32 * c + row(r0 + i);
+        if (ml + dm >= out.M) continue;
+        const int64_t e = el + static_cast<int64_t>(dm) * out.O;
+        float v = val(c, r0 + i);
+        if constexpr (out_res(kOut)) v = add_relu(v, rv[i]);
+        if constexpr (out_f32(kOut)) {
+          if (check_store(kSiteStoreY, e, 1, n)) __builtin_nontemporal_store(v, out.y + e);
+        }
+        if constexpr (kCode == 8) {
+          if (check_store(kSiteStoreY, e, 1, n))
+            __builtin_nontemporal_store(static_cast<uint8_t>(qcode<kRcp>(v, qs)), out.q + e);
+        } else if constexpr (kCode == 4) {
+          const unsigned b = pair_nibbles(qcode<kRcp>(v, qs));
+          if ((o & 1) == 0 && check_store(kSiteStoreY, e >> 1, 1, (n + 1) / 2))
+            __builtin_nontemporal_store(static_cast<uint8_t>(b), out.q + (e >> 1));
+        }
       }
     }
   }
 }
 
 // A workgroup's residual values of a staged tile, in the order store_staged
-// uses them: requested before the tile's last matrix work, so that the store
-// phase does not wait for memory once per block (a first-stage ResNet-50
-// block at batch 64, whose last layer reads and writes 206 MB each: 211 ->
-// 150 us, the layer 151 -> 90).
+// uses them: requested all at once, before or behind the tile's last matrix
+// work, so that the store phase does not wait for memory once per block (a
+// first-stage ResNet-50 block at batch 64, whose last layer reads and writes
+// 206 MB each: 211 -> 150 us, the layer 151 -> 90).
 // kBlocks of the wave's kNB blocks (row stride), from block c0 on.
 template <int kOut, int kNWO, int kNB, int kBlocks = kNB>
 struct ResTile {

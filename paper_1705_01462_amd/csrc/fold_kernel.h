@@ -119,7 +119,8 @@ namespace {
 
 using namespace ig;
 
-template <int kBits, int kNWO, int kNB, int kCM, int kOut, bool kDfp, int kG, int kNWK = 1>
+// kPre: a residual is requested before the last step's matrix work.
+template <int kBits, int kNWO, int kNB, int kCM, int kOut, bool kDfp, int kG, int kNWK = 1, bool kPre = false>
 __global__ __launch_bounds__(kThreads * kNWK, kNB <= 2 ? 2 : 1) void fold_conv_kernel(FoldArgs a) {
   constexpr int kNWM = 4 / kNWO;
   constexpr int kTO = 32 * kNWO;
@@ -417,12 +418,11 @@ __global__ __launch_bounds__(kThreads * kNWK, kNB <= 2 ? 2 : 1) void fold_conv_k
     } else {
       finish(I0{}, ks);
     }
-  } else if constexpr (kPlanes == 1 && out_res(kOut)) {
-    // The last step prefetches and publishes nothing; a residual is requested
-    // before its matrix work.
+  } else if constexpr (kPre) {
+    // The last step prefetches and publishes nothing.
     auto last = [&](auto U) {
       constexpr int u = decltype(U)::value;
-      if (a.staged) res.load(a.res, a.x.M, a.x.O, m0, o0 - 32 * wo, tid);
+      res.load(a.res, a.x.M, a.x.O, m0, o0 - 32 * wo, tid);
       __builtin_amdgcn_sched_barrier(0);
       compute(u, wring[u]);
     };
@@ -440,6 +440,7 @@ __global__ __launch_bounds__(kThreads * kNWK, kNB <= 2 ? 2 : 1) void fold_conv_k
     // One way into the epilogue: a second one costs registers, which spill
     // with three planes' 96 accumulators and cost one plane a workgroup per
     // compute unit (14.7 -> 15.2 us, 128 -> 128 channels, 3x3, 28 x 28, batch 64).
+    // A residual is requested behind the last step.
     for (; ks + 2 <= nk; ks += 2) {
       step(I0{}, ks);
       step(I1{}, ks + 1);
@@ -469,7 +470,7 @@ __global__ __launch_bounds__(kThreads * kNWK, kNB <= 2 ? 2 : 1) void fold_conv_k
   } else {
     // locals: a byte store may alias anything, including the argument block
     const OutPtrs out{a.y, a.qo, a.x.M, a.x.O, a.res};
-    const bool staged = a.staged != 0;
+    const bool staged = kPre || a.staged != 0;
     if constexpr (kNWK == 2) {
       // The sets exchange a block each through LDS and add (integers, exact):
       // set 0 finishes the waves' first blocks, set 1 the second.
@@ -550,6 +551,23 @@ fgq_status launch_cfg(const FoldArgs& a0, hipStream_t st) {
         hipLaunchKernelGGL((fold_conv_kernel<kBits, kNWO, kNB, 0, kOut, kDfp, kG, 2>), grid, dim3(2 * kThreads), 0, st, a);
       else
         hipLaunchKernelGGL((fold_conv_kernel<kBits, kNWO, kNB, 1, kOut, kDfp, kG, 2>), grid, dim3(2 * kThreads), 0, st, a);
+      return last_launch();
+    }
+  }
+  // A residual requested ahead of the last step costs the one-plane kernel two
+  // of its five workgroups a unit (100 -> 156 registers).  It pays on staged
+  // outputs of short reductions, whose time is the residual and the output (1
+  // to 2 steps, up to 768 tiles, 1.03 to 1.07 times as fast as behind the
+  // step; 9 to 16 steps 1.00 to 1.04, more tiles 0.98); single stores, the
+  // form of a channel count off 4, need the workgroups (11760 rows, 576 ->
+  // 1645: 71 us before it was requested early, 96 after).
+  if constexpr (kDfp && out_res(kOut)) {
+    const int nk = (a.x.K + kKT - 1) / kKT;
+    if (a.staged && c_mode(a.x.C) <= 1 && (nk <= 8 || (nk <= 16 && n <= 3LL * device_cus()))) {
+      if (a.x.C >= kKT)
+        hipLaunchKernelGGL((fold_conv_kernel<kBits, kNWO, kNB, 0, kOut, kDfp, kG, 1, true>), grid, dim3(kThreads), 0, st, a);
+      else
+        hipLaunchKernelGGL((fold_conv_kernel<kBits, kNWO, kNB, 1, kOut, kDfp, kG, 1, true>), grid, dim3(kThreads), 0, st, a);
       return last_launch();
     }
   }

@@ -82,7 +82,8 @@ constexpr int kStepBytes = 64 * 16;  // codes of one channel tile, one 128-wide 
 // activation stages and its loads two steps ahead (see fold_kernel.h); their
 // fp32 partial sums of a block are added once, so no value passes through
 // more roundings than with one set.
-template <int kBits, int kNWO, int kNB, int kCM, int kOut, int kNWK = 1, bool kF8 = kBits == 4>
+// kPre: a residual is requested before the last step's matrix work.
+template <int kBits, int kNWO, int kNB, int kCM, int kOut, int kNWK = 1, bool kF8 = kBits == 4, bool kPre = false>
 __global__ __launch_bounds__(kThreads * kNWK, 2) void group_conv_kernel(GroupArgs a) {
   constexpr int kNWM = 4 / kNWO;
   constexpr int kTO = 32 * kNWO;
@@ -275,11 +276,11 @@ __global__ __launch_bounds__(kThreads * kNWK, 2) void group_conv_kernel(GroupArg
     __syncthreads();
 #pragma unroll
     for (int r = 0; r < 16; ++r) acc[0][r] = (wk == 0 ? acc[0][r] : acc[1][r]) + take[64 * r];
-  } else if constexpr (out_res(kOut)) {
-    // The last step prefetches and publishes nothing; the residual is
-    // requested before its matrix work.
+  } else if constexpr (kPre) {
+    // The last step prefetches and publishes nothing.
     auto last = [&](auto U) {
       constexpr int u = decltype(U)::value;
+      // (always true; as a branch of its own it keeps the uint4 kernel at 168 registers)
       if (a.staged) res.load(a.res, a.x.M, a.x.O, m0, o0 - 32 * wo, tid);
       __builtin_amdgcn_sched_barrier(0);
       compute(u, cring[u], aring[u]);
@@ -300,13 +301,14 @@ __global__ __launch_bounds__(kThreads * kNWK, 2) void group_conv_kernel(GroupArg
       step(I1{}, ks + 1);
     }
     if (ks < nk) step(I0{}, ks);
+    if (a.staged) res.load(a.res, a.x.M, a.x.O, m0, o0 - 32 * wo, tid);
   }
 
   // ---- epilogue: lane holds rows m of channel o.
   const int o = o0 + lane % 32;
   // locals: a byte store may alias anything, including the argument block
   const OutPtrs out{a.y, a.qo, a.x.M, a.x.O, a.res};
-  const bool staged = a.staged != 0;
+  const bool staged = kPre || a.staged != 0;
   with_out_scale<kOut>(os, [&](const QScale& qs, auto rcp) {
     constexpr bool kR = decltype(rcp)::value;
     auto val = [&](int c, int r) { return acc[c][r] * sx; };
@@ -343,6 +345,24 @@ fgq_status launch_cfg(const GroupArgs& a0, hipStream_t st) {
       else
         hipLaunchKernelGGL((group_conv_kernel<kBits, kNWO, kNB, 0, kOut, 1, false>), dim3(static_cast<uint32_t>(n)),
                            dim3(kThreads), 0, st, a);
+      return last_launch();
+    }
+  }
+  // A residual requested ahead of the last step costs a workgroup of the three
+  // (8 bits: 161 -> 192 registers) or four a unit.  It pays where the residual
+  // and the output are the layer's time (1 to 2 steps, 1.02 to 1.06 times as
+  // fast as behind the step; up to 768 tiles of 3 to 8 steps 1.02 to 1.06) and
+  // not on long reductions (1500 tiles of 5 to 8 steps 0.92 to 0.97, of 9 and
+  // more 0.91 to 0.97), nor in front of single stores (a channel count off 4),
+  // which need the workgroups.
+  if constexpr (out_res(kOut)) {
+    if (a.staged && (a.x.K <= 2 * kKT || (a.x.K <= 8 * kKT && n <= 3LL * device_cus()))) {
+      if (a.x.C < kKT)
+        hipLaunchKernelGGL((group_conv_kernel<kBits, kNWO, kNB, 1, kOut, 1, kBits == 4, true>),
+                           dim3(static_cast<uint32_t>(n)), dim3(kThreads), 0, st, a);
+      else
+        hipLaunchKernelGGL((group_conv_kernel<kBits, kNWO, kNB, 0, kOut, 1, kBits == 4, true>),
+                           dim3(static_cast<uint32_t>(n)), dim3(kThreads), 0, st, a);
       return last_launch();
     }
   }

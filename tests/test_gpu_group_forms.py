@@ -30,6 +30,7 @@ CASES = [
     (1, 66, 67, 192, 132, 1),    # one set, 1.5 steps
     (2, 97, 101, 64, 130, 1),    # one set, half a step: the one-step form
     (2, 97, 101, 128, 96, 3),    # one set, 9 steps
+    (1, 66, 67, 192, 130, 1),    # single stores, residual values in batches
 ]
 
 

@@ -135,3 +135,27 @@ def test_one_unaligned_output():
 ])
 def test_fixed_point_two_sets(case, bits):
     test_fixed_point(case, bits)
+
+
+@pytest.mark.parametrize("bits", [8, 4])
+@pytest.mark.parametrize("case", [
+    (5, 57, 60, 2192, 68, 1, 1),   # 18 steps: the residual behind the last
+    (5, 57, 60, 2192, 67, 1, 1),   # the same, single stores (no 4-bit codes)
+    (5, 57, 60, 208, 72, 1, 1),    # two steps: ahead of it
+    (5, 57, 60, 80, 30, 1, 1),     # one, single stores of one channel wave
+])
+def test_fixed_point_residual(case, bits):
+    # tiled, one wave set: codes and residual outputs against the fp32 output
+    B, H, W, C, O, R, st = case
+    q = torch.randint(0, 256, (B * H * W * C * bits // 8,), dtype=torch.uint8, device="cuda",
+                      generator=torch.Generator(device="cuda").manual_seed(2))
+    t, a, _ = oracle.ternarize(fi.he_weights(O, C, R, R, "wavek-res"), 4)
+    codes = dev(oracle.pack_codes(t))
+    prep = fgq.fgq_prepare_weights_dfp(codes, dev(a), O, C, 4, 8)
+    args = (q, bits, torch.tensor([0.004], device="cuda"), (B, H, W, C), codes, prep, O, R, R, st, 0, 4)
+
+    def residual(res, b, so, y=None):
+        return fgq.fgq_conv2d_dfp_residual(*args, res, b, so, y=y)
+
+    run_kinds(lambda: fgq.fgq_conv2d_dfp(*args), lambda b, so: fgq.fgq_conv2d_dfp(*args, b, so), residual, O,
+              B * H * W, (B, H, W, O))
