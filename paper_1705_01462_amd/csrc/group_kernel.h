@@ -28,7 +28,10 @@
 // channels, 7 x 7, with two wave sets: 31.9 -> 20.3).  An fp32 output of one
 // K step keeps the int8 form: it is bound by its stores, which leave at a
 // better rate behind the longer matrix part (64 -> 256 channels, 56 x 56,
-// batch 64: 35.4 us against 38.1).
+// batch 64: 35.4 us against 38.1).  So do large outputs of two K steps and,
+// stored singly (a channel count off 4), of three (24336 rows, 256 -> 1949:
+// 64.5 us against 74.3; 49708 rows, 320 -> 487: 31.3 against 38.1; below 11 M
+// values of two steps the e4m3 form is 3 to 17% faster).
 //
 // Staging of activations (LDS) follows the folded-scale kernel; see
 // igemm.h.  The weights are read as the 2-bit codes (one 16-byte load per
@@ -338,7 +341,10 @@ fgq_status launch_cfg(const GroupArgs& a0, hipStream_t st) {
     }
   }
   if constexpr (kBits == 4 && kOut == 0) {
-    if (a.x.K <= kKT) {  // one step
+    // fp32 outputs of up to three K steps whose stores are the layer: see above
+    const int64_t els = static_cast<int64_t>(a.x.M) * a.x.O;
+    if (a.x.K <= kKT || (a.x.K <= 2 * kKT && els >= (a.staged ? 16000000 : 11000000)) ||
+        (a.x.K <= 3 * kKT && !a.staged && els >= 16000000)) {
       if (a.x.C < kKT)
         hipLaunchKernelGGL((group_conv_kernel<kBits, kNWO, kNB, 1, kOut, 1, false>), dim3(static_cast<uint32_t>(n)),
                            dim3(kThreads), 0, st, a);

@@ -31,6 +31,9 @@ CASES = [
     (2, 97, 101, 64, 130, 1),    # one set, half a step: the one-step form
     (2, 97, 101, 128, 96, 3),    # one set, 9 steps
     (1, 66, 67, 192, 130, 1),    # single stores, residual values in batches
+    (2, 97, 101, 192, 622, 1),   # two steps, single stores of 12 M values: the int8 form
+    (2, 97, 101, 320, 820, 1),   # three steps, 16 M values: staged, the 4-bit form
+    (2, 97, 101, 320, 818, 1),   # the same, single stores: the int8 form
 ]
 
 
