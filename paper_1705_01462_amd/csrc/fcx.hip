@@ -268,7 +268,7 @@ fgq_status launch_fcx(const uint8_t* q, const float* sx, const void* prepared, b
   a.y = out.bits == 0 ? out.y : nullptr;
   a.code_bits = out.bits;
   a.qo = out.bits ? out.q : nullptr;
-  a.vec = g.O % 4 == 0 && al(a.y, 16) && al(a.qo, out.bits == 4 ? 2 : 4);
+  a.vec = g.O % 4 == 0 && al(a.qo, out.bits == 4 ? 2 : 4);
   a.M = static_cast<int32_t>(g.M);
   a.K = static_cast<int32_t>(g.K);
   a.O = static_cast<int32_t>(g.O);

@@ -200,7 +200,7 @@ fgq_status launch_splitk_reduce(const int32_t* part, int32_t splits, bool dfp, i
 // The same layers with K divided among a workgroup's waves (wavek.h), for
 // few tiles: whether a shape takes it, and the launch (kind: PrepKind of the
 // prepared buffer; callers check that kind's own *_supported first).
-bool wavek_pick(const ConvGeom& g, int kind);
+bool wavek_pick(const ConvGeom& g, int kind, int out_bits);
 fgq_status launch_wavek(const uint8_t* q, const float* sx, const void* prepared, int kind, const ConvGeom& g,
                         const LayerOut& out, hipStream_t st);
 // The one-plane layer on images of four 8-bit channels (tinyc.hip).

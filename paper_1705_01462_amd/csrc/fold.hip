@@ -12,7 +12,7 @@ bool fold_supported(const ConvGeom& g, const uint8_t* q) {
 
 fgq_status launch_fold_conv(const uint8_t* q, const float* sx, const void* prepared,
                             const ConvGeom& g, const LayerOut& out, hipStream_t st) {
-  if (wavek_pick(g, kPrepFold)) return launch_wavek(q, sx, prepared, kPrepFold, g, out, st);
+  if (wavek_pick(g, kPrepFold, out.bits)) return launch_wavek(q, sx, prepared, kPrepFold, g, out, st);
   const PreparedLayout L = prepared_layout(g.O, g.K, g.G);
   const char* base = static_cast<const char*>(prepared);
   FoldArgs a;

@@ -13,7 +13,7 @@ bool fold_dfp_supported(const ConvGeom& g, const uint8_t* q) {
 fgq_status launch_fold_dfp_conv(const uint8_t* q, const float* sx, const void* prepared,
                                 const ConvGeom& g, const LayerOut& out, hipStream_t st) {
   if (tinyc_supported(g, q, out)) return launch_tinyc(q, sx, prepared, g, out, st);
-  if (wavek_pick(g, kPrepDfp)) return launch_wavek(q, sx, prepared, kPrepDfp, g, out, st);
+  if (wavek_pick(g, kPrepDfp, out.bits)) return launch_wavek(q, sx, prepared, kPrepDfp, g, out, st);
   const PreparedLayout L = prepared_layout_dfp(g.O, g.K, g.G);
   const char* base = static_cast<const char*>(prepared);
   FoldArgs a;

@@ -12,7 +12,7 @@ bool group_supported(const ConvGeom& g, const uint8_t* q) {
 
 fgq_status launch_group_conv(const uint8_t* q, const float* sx, const void* prepared,
                              const ConvGeom& g, const LayerOut& out, hipStream_t st) {
-  if (wavek_pick(g, kPrepGroup)) return launch_wavek(q, sx, prepared, kPrepGroup, g, out, st);
+  if (wavek_pick(g, kPrepGroup, out.bits)) return launch_wavek(q, sx, prepared, kPrepGroup, g, out, st);
   const PreparedLayout L = prepared_layout(g.O, g.K, g.G);
   const char* base = static_cast<const char*>(prepared);
   GroupArgs a;

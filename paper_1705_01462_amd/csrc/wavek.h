@@ -49,7 +49,7 @@ struct WavekArgs {
   uint8_t* q;             // code output, or null
   const float* oscale;    // its scale
   int32_t code_bits;      // 0, 8 or 4
-  int32_t vec;            // four channels of a row are one aligned piece in every tensor
+  int32_t vec;            // codes of four channels of a row are one aligned piece
   int32_t weights_bytes, alpha_bytes, nks, O32;
   uint32_t inv_c, inv_s;  // ceil(2^32 / C), ceil(2^32 / S) (S > 1)
 };
@@ -65,18 +65,23 @@ struct PieceOut {
   float* y;         // fp32 output, or null
   uint8_t* q;       // code output, or null
   int32_t code_bits;
-  bool vec;         // pieces are whole and aligned in every output
+  bool vec;         // code pieces are whole and aligned
 };
 
 // Channels e .. e+3 of the output (n elements), of which `left` are in the row.
+// fp32 pieces are 16 bytes at any 4-byte boundary, which the memory pipeline
+// takes whole: as single stores (and single loads of the bias and the scales)
+// the channel counts off 4 took up to 1.4 times as long as the tiled kernel
+// (fixed-point scales, 2037 rows, 256 -> 218: 4.6 us there, 6.3; 1568 rows,
+// 176 -> 242: 4.8 there, 5.1 singly, 4.3 here).
 template <bool kR>
 __device__ inline void store_piece(const PieceOut& out, const QScale& qs, const float __attribute__((ext_vector_type(4))) v,
                                    int64_t e, int left, int64_t n) {
-  typedef float v4f __attribute__((ext_vector_type(4)));
+  typedef float v4fu __attribute__((ext_vector_type(4), aligned(4)));  // any row alignment
   const int nv = left < 4 ? left : 4;
   if (out.y) {
-    if (out.vec) {
-      if (check_store(kSiteStoreY, e, 4, n)) __builtin_nontemporal_store(v, reinterpret_cast<v4f*>(out.y + e));
+    if (nv == 4) {
+      if (check_store(kSiteStoreY, e, 4, n)) __builtin_nontemporal_store(static_cast<v4fu>(v), reinterpret_cast<v4fu*>(out.y + e));
     } else {
 #pragma unroll
       for (int c = 0; c < 4; ++c)
@@ -117,6 +122,8 @@ __global__ __launch_bounds__(64 * kWO * kWK, 2) void wavek_kernel(WavekArgs a) {
   constexpr int kCh = (kChunks + kWG - 1) / kWG;
   typedef typename std::conditional<kBits == 8, v4i, v2i>::type raw_t;
   typedef float v4f __attribute__((ext_vector_type(4)));
+  typedef float v4fu __attribute__((ext_vector_type(4), aligned(4)));  // any row alignment
+  typedef int v4iu __attribute__((ext_vector_type(4), aligned(4)));
   __shared__ __attribute__((aligned(16))) int red[kWO * kWK][32 * kPitch];
 
   const int tid = threadIdx.x;
@@ -231,32 +238,21 @@ __global__ __launch_bounds__(64 * kWO * kWK, 2) void wavek_kernel(WavekArgs a) {
 #pragma unroll
     for (int j = 0; j < kPlanes; ++j) biasv[i][j] = v4i{0, 0, 0, 0};
     if (a.res && in) {
-      if (vec) {
-        if (ch < O && check_store(kSiteStoreY, e, 4, static_cast<int64_t>(M) * O))  // the output's extent
-          resv[i] = __builtin_nontemporal_load(reinterpret_cast<const v4f*>(a.res + e));
+      if (ch + 4 <= O) {
+        if (check_store(kSiteStoreY, e, 4, static_cast<int64_t>(M) * O))  // the output's extent
+          resv[i] = __builtin_nontemporal_load(reinterpret_cast<const v4fu*>(a.res + e));
       } else {
 #pragma unroll
-        for (int c = 0; c < 4; ++c)
+        for (int c = 0; c < 3; ++c)
           if (ch + c < O && check_store(kSiteStoreY, e + c, 1, static_cast<int64_t>(M) * O)) resv[i][c] = a.res[e + c];
       }
     }
-    if constexpr (kMode != 2) {
-      if (vec) {  // bias and scale start 256-byte aligned in the prepared buffer
-        if (t < kChunks && ch < O) {
-          if constexpr (kMode == 0) scv[i] = *reinterpret_cast<const v4f*>(a.scale + ch);
-          if constexpr (kBits == 8)
+    if constexpr (kMode != 2) {  // (up to three values past the last channel: still inside the prepared buffer)
+      if (t < kChunks && ch < O) {
+        if constexpr (kMode == 0) scv[i] = *reinterpret_cast<const v4f*>(a.scale + ch);
+        if constexpr (kBits == 8)
 #pragma unroll
-            for (int j = 0; j < kPlanes; ++j) biasv[i][j] = *reinterpret_cast<const v4i*>(a.bias + j * O + ch);
-        }
-      } else {
-#pragma unroll
-        for (int c = 0; c < 4; ++c)
-          if (t < kChunks && ch + c < O) {
-            if constexpr (kMode == 0) scv[i][c] = a.scale[ch + c];
-            if constexpr (kBits == 8)
-#pragma unroll
-              for (int j = 0; j < kPlanes; ++j) biasv[i][j][c] = a.bias[j * O + ch + c];
-          }
+          for (int j = 0; j < kPlanes; ++j) biasv[i][j] = *reinterpret_cast<const v4iu*>(a.bias + j * O + ch);
       }
     }
   }

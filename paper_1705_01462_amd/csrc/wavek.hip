@@ -20,12 +20,15 @@ namespace fgq {
 // much again (the fragment loads of one already take most of its L1), which
 // only a long reduction repays.  One K step leaves nothing to share, and
 // three planes take longer to fetch than two to four steps of the tiled
-// kernel.
-bool wavek_pick(const ConvGeom& g, int kind) {
+// kernel.  Two whole steps of one plane into a larger fp32 output leave the
+// tiled kernel little to lose (M 1528, O 158: 4.5 -> 5.0; M 34, O 68: 3.8 ->
+// 4.3; M 3904, O 114: 4.6 -> 5.2; up to 32 rows or 64 channels 0.52 to 0.97).
+bool wavek_pick(const ConvGeom& g, int kind, int out_bits) {
   if (g.C % 16 != 0) return false;  // other C: a fragment's 16 k are not one run of channels
   const int64_t nk = ceil_div(g.K, 128);
   const int64_t wgs = ceil_div(g.M, 32) * ceil_div(g.O, 32 * wavek_channel_waves(static_cast<int>(nk)));
   const int64_t cus = ig::device_cus();
+  if (kind == kPrepDfp && out_bits == 0 && g.K == 256 && g.M > 32 && g.O > 64) return false;
   if (wgs <= cus) return nk >= (kind == kPrepFold ? 5 : 2);
   return wgs <= 2 * cus && nk >= (kind == kPrepGroup ? 8 : 16);
 }
@@ -46,7 +49,7 @@ WavekArgs make_args(const uint8_t* q, const float* sx, const ConvGeom& g, const 
   a.q = a.code_bits ? out.q : nullptr;
   a.oscale = out.scale;
   const auto al = [](const void* p, uintptr_t n) { return reinterpret_cast<uintptr_t>(p) % n == 0; };
-  a.vec = g.O % 4 == 0 && al(a.y, 16) && al(a.res, 16) && al(a.q, a.code_bits == 4 ? 2 : 4);
+  a.vec = g.O % 4 == 0 && al(a.q, a.code_bits == 4 ? 2 : 4);
   a.weights_bytes = a.alpha_bytes = a.nks = a.O32 = 0;
   a.inv_c = static_cast<uint32_t>(((1ULL << 32) + g.C - 1) / g.C);
   a.inv_s = g.S > 1 ? static_cast<uint32_t>(((1ULL << 32) + g.S - 1) / g.S) : 0;
