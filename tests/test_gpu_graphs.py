@@ -1,11 +1,13 @@
 """The hot path captured in a HIP graph (as the benchmark runs it): every
 replay, with eager work and synchronizations in between, must reproduce the
 eager results bit for bit.  Covers the dynamic-scale quantization (two
-passes), the folded and per-group convolutions, the row-walking folded
-kernel (a 1x1 layer with K = 64 over many row tiles), the fused 8-bit
-output, the fixed-point convolution, and the split-K GEMMs with their
-reduction (none of them may record a memset); and independent batches as
-concurrent chains of one graph.
+passes), the folded, per-group and fixed-point convolutions at few rows (K
+divided over a workgroup's waves) and, on a larger map, on the tiled kernels
+(the per-group and fixed-point ones with two wave sets), the row-walking folded
+kernel (a 1x1 layer with K = 64 over many row tiles), the fused 8-bit output,
+the GEMMs at few rows in one launch, and the split-K GEMMs with their reduction
+(none of them may record a memset); and independent batches as concurrent
+chains of one graph.
 """
 import numpy as np
 import pytest
@@ -36,6 +38,22 @@ def test_graph_replays_match_eager():
     pf = fgq.fgq_prepare_weights(cf, af, OF, KF, GF)
     pfd = fgq.fgq_prepare_weights_dfp(cf, af, OF, KF, GF, 8)
     xf = torch.from_numpy(fi.relu_gauss((M, KF), "graph-fc")).cuda()
+    # past the one-launch rule: the split GEMM and its reduction
+    MS, KS, OS = 64, 9216, 512
+    wsp = fi.gauss_weights(OS, KS, 0.01, "graph-split")
+    csp, asp, _ = fgq.fgq_ternarize(torch.from_numpy(wsp).cuda(), GF)
+    psp = fgq.fgq_prepare_weights(csp, asp, OS, KS, GF)
+    pspd = fgq.fgq_prepare_weights_dfp(csp, asp, OS, KS, GF, 8)
+    xs = torch.from_numpy(fi.relu_gauss((MS, KS), "graph-split")).cuda()
+    # past the rule that divides K (more than 512 tiles of 32 rows): the tiled kernels
+    HT, CT, OT = 47, 128, 260
+    xt = torch.from_numpy(fi.relu_gauss((1, HT, HT, CT), "graph-tiled")).cuda()
+    tiled = {}
+    for G in (4, 64):
+        wt = fi.he_weights(OT, CT, R, S, "graph-tiled", G)
+        ct, at, _ = fgq.fgq_ternarize(torch.from_numpy(wt).cuda(), G)
+        tiled[G] = (ct, at, fgq.fgq_prepare_weights(ct, at, OT, K, G),
+                    fgq.fgq_prepare_weights_dfp(ct, at, OT, K, G, 8))
     # a 1x1 layer with K = 64 and 1568 row/channel tiles: the row-walking kernel
     BR, HR, CR, OR = 16, 56, 64, 256
     wr = fi.he_weights(OR, CR, 1, 1, "graph-rows", 4)
@@ -53,6 +71,9 @@ def test_graph_replays_match_eager():
     qr = torch.empty(xr.numel(), dtype=torch.uint8, device="cuda")
     sxr = torch.empty(1, device="cuda")
     wsr = torch.empty(fgq.fgq_quantize_ws_bytes(xr.numel()), dtype=torch.uint8, device="cuda")
+    qs, qt = (torch.empty(v.numel(), dtype=torch.uint8, device="cuda") for v in (xs, xt))
+    sxs, sxt = torch.empty(1, device="cuda"), torch.empty(1, device="cuda")
+    wss, wst = (torch.empty(fgq.fgq_quantize_ws_bytes(v.numel()), dtype=torch.uint8, device="cuda") for v in (xs, xt))
     osc = torch.full((1,), 0.05, device="cuda")
     Ho = H
     for key in ("y4", "y64", "yd4", "yd64"):
@@ -63,6 +84,11 @@ def test_graph_replays_match_eager():
     outs["yr"] = torch.empty((BR, HR, HR, OR), device="cuda")
     outs["qr8"] = torch.empty(BR * HR * HR * OR, dtype=torch.uint8, device="cuda")
     wsg = torch.empty(max(fgq.fgq_gemm_ws_bytes(M, KF, OF, GF, False), 4), dtype=torch.uint8, device="cuda")
+    outs["gs"], outs["gsd"] = (torch.empty((MS, OS), device="cuda") for _ in range(2))
+    for key in ("t4", "t64", "td4", "td64"):
+        outs[key] = torch.empty((1, HT, HT, OT), device="cuda")
+    wsgs, wsgsd = (torch.empty(max(fgq.fgq_gemm_ws_bytes(MS, KS, OS, GF, dfp), 4), dtype=torch.uint8, device="cuda")
+                   for dfp in (False, True))
     wsgd = torch.empty(max(fgq.fgq_gemm_ws_bytes(M, KF, OF, GF, True), 4), dtype=torch.uint8, device="cuda")
 
     def step():
@@ -77,6 +103,14 @@ def test_graph_replays_match_eager():
                          q_out=outs["q8"])
         fgq.fgq_gemm_ws(qf, 8, sxf, M, KF, cf, af, OF, GF, prepared=pf, out=outs["gf"], ws=wsg)
         fgq.fgq_gemm_dfp_ws(qf, 8, sxf, M, KF, cf, pfd, OF, GF, out=outs["gfd"], ws=wsgd)
+        fgq.fgq_quantize_act(xs, 8, q=qs, scale_out=sxs, ws=wss)
+        fgq.fgq_gemm_ws(qs, 8, sxs, MS, KS, csp, asp, OS, GF, prepared=psp, out=outs["gs"], ws=wsgs)
+        fgq.fgq_gemm_dfp_ws(qs, 8, sxs, MS, KS, csp, pspd, OS, GF, out=outs["gsd"], ws=wsgsd)
+        fgq.fgq_quantize_act(xt, 8, q=qt, scale_out=sxt, ws=wst)
+        for G in (4, 64):
+            ct, at, pt, ptd = tiled[G]
+            fgq.fgq_conv2d(qt, 8, sxt, (1, HT, HT, CT), ct, at, OT, R, S, 1, 1, G, prepared=pt, y=outs[f"t{G}"])
+            fgq.fgq_conv2d_dfp(qt, 8, sxt, (1, HT, HT, CT), ct, ptd, OT, R, S, 1, 1, G, out=outs[f"td{G}"])
         fgq.fgq_quantize_act(xr, 8, q=qr, scale_out=sxr, ws=wsr)
         fgq.fgq_conv2d(qr, 8, sxr, (BR, HR, HR, CR), cr, ar, OR, 1, 1, 1, 0, 4, prepared=pr, y=outs["yr"])
         fgq.fgq_conv2d_q(qr, 8, sxr, (BR, HR, HR, CR), cr, ar, OR, 1, 1, 1, 0, 4, 8, osc, prepared=pr,
