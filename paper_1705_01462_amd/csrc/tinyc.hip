@@ -24,9 +24,11 @@
 // product of two fp32 values, rounded once either way, at a third of the
 // instructions.
 //
-// Bound: the codes' vector work (eight instructions an output) beside the
-// output's bytes, 51 MB for a 7x7 layer of 64 channels on 64 images of
-// 224 x 224: 56.9 us gathered tap by tap, 33.2 here.
+// Bound: a unit's phases one after another, three workgroups a unit covering
+// part of it.  On a 7x7 layer of 64 channels, 64 images of 224 x 224 (56.9 us
+// gathered tap by tap, 33.0 here): vector work 21.6 us of the SIMDs (14.5
+// instructions an output wave), matrix work 6.0, the bytes 13.6 at the copy
+// rate, bank conflicts of the tile 8.
 #include "fold_kernel.h"
 
 namespace fgq {
