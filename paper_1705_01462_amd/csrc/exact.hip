@@ -67,7 +67,7 @@ __device__ inline int64_t a_index(const ConvGeom& g, int64_t m, int64_t k) {
 // its time on: 86.0 -> 35.1 us a call on a 3x3 layer of 40 -> 100 channels,
 // 8 x 29 x 31, G = 4.  That layer has 226 workgroups, at most one wave a SIMD,
 // which issues vector instructions in 52% of its cycles and waits in 28%; with
-// four (128 -> 128 channels, 28 x 28, 32 images) it is 83% of the issue rate.
+// three (128 -> 128 channels, 28 x 28, 32 images) it is 83% of the issue rate.
 //
 // kVec: C % 4 == 0, so four consecutive k share one tap and are contiguous.
 // kDot4: G % 4 == 0, so groups end on words of four k.
