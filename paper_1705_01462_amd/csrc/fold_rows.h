@@ -32,7 +32,8 @@ namespace {
 
 using namespace ig;
 
-template <int kBits, int kCM, int kOut>
+// kTwo: single fp32 stores, behind both blocks' matrix work.
+template <int kBits, int kCM, int kOut, bool kTwo = false>
 __global__ __launch_bounds__(kThreads, 2) void fold_rows_kernel(FoldArgs a) {
   constexpr int kNWO = 4, kNB = 2, kPlanes = 3;
   constexpr int kTO = 32 * kNWO;  // 128 channels
@@ -101,6 +102,31 @@ __global__ __launch_bounds__(kThreads, 2) void fold_rows_kernel(FoldArgs a) {
       xs.init(a.x, m0 + mstride * kTM, tid, 0);
       xs.load(a.x);
     }
+    if constexpr (kTwo) {
+      v16i acc[kNB][kPlanes];
+#pragma unroll
+      for (int c = 0; c < kNB; ++c)
+#pragma unroll
+        for (int j = 0; j < kPlanes; ++j)
+#pragma unroll
+          for (int r = 0; r < 16; ++r) acc[c][j][r] = bias[j];
+#pragma unroll
+      for (int h = 0; h < 4; ++h)
+#pragma unroll
+        for (int c = 0; c < kNB; ++c) {
+          const v4i xf = *reinterpret_cast<const v4i*>(lds + afrag[c][h]);
+#pragma unroll
+          for (int j = 0; j < kPlanes; ++j)
+            acc[c][j] = __builtin_amdgcn_mfma_i32_32x32x32_i8(xf, w[j][h], acc[c][j], 0, 0, 0);
+        }
+      store_direct<kOut, kNB, true>(out, QScale{}, m0, o, lane, [&](int c, int r) {
+        const float f2 = static_cast<float>(acc[c][2][r]);
+        const float f1 = static_cast<float>(acc[c][1][r]);
+        const float f0 = static_cast<float>(acc[c][0][r]);
+        return fmaf(f2, c2, fmaf(f1, c1, f0 * c0));
+      });
+      continue;
+    }
     // One 32-row block at a time, matrix work and stores: its 48 accumulators
     // leave registers for the residual tile and the resident weights.
 #pragma unroll
@@ -148,6 +174,18 @@ fgq_status launch_rows_bits(const FoldArgs& a0, hipStream_t st) {
   const int64_t n = per_o * a.x.n_otiles;
   if (n > 0x7fffffffLL) return FGQ_ERR_SHAPE;
   const dim3 grid(static_cast<uint32_t>(n));
+  // Stored singly (a channel count off 4), fp32 outputs of up to 128 channels
+  // are 1.03 to 1.06 times as fast (at most 1.17) behind both blocks' matrix
+  // work; whole pieces 0.97 to 1.00 (4 bits), 0.98 to 1.00 (8 bits).
+  if constexpr (kOut == 0) {
+    if (!a.staged) {
+      if (c_mode(a.x.C) == 0)
+        hipLaunchKernelGGL((fold_rows_kernel<kBits, 0, kOut, true>), grid, dim3(kThreads), 0, st, a);
+      else
+        hipLaunchKernelGGL((fold_rows_kernel<kBits, 1, kOut, true>), grid, dim3(kThreads), 0, st, a);
+      return last_launch();
+    }
+  }
   if (c_mode(a.x.C) == 0)
     hipLaunchKernelGGL((fold_rows_kernel<kBits, 0, kOut>), grid, dim3(kThreads), 0, st, a);
   else

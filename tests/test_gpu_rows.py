@@ -51,6 +51,7 @@ CASES = [
     (8, 112, 112, 16, 96, 4, 4),     # K = 16, one partial channel tile, uint4
     (12, 57, 57, 32, 200, 32, 8),    # ragged M and O, G = 32 (8-bit codes stored directly: O % 16 != 0)
     (24, 56, 56, 64, 99, 4, 8),      # odd O: every output stored directly from registers
+    (7, 99, 97, 32, 70, 4, 4),       # the same at uint4, ragged M
 ]
 
 
